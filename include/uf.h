@@ -63,7 +63,12 @@ enum { UF_TURB_OFF = 0, UF_TURB_KOMEGA = 1 };
 /* Pressure CG preconditioner: none, Jacobi, the first- or second-order
  * approximate inverse M^-1 = K^T K of Sec. 3 (full products, see
  * uf_config.ai_omega; AI2 takes two passes through the grid's scratch
- * vector), or a geometric multigrid V-cycle. */
+ * vector), or a geometric multigrid V-cycle.  With UF_PC_MG and criterion 0
+ * the solve itself is direct where that is the faster way (nx <= 512, ny +
+ * nz <= 2048, fields below 4 GiB): sine and cosine transforms along y and z
+ * and tridiagonal systems along x, repeated on the residual until the same
+ * stopping test holds (one or two iterations in FP32; cg_iters counts
+ * them).  The operator uf_apply_operator applies stays the V-cycle. */
 enum { UF_PC_NONE = 0, UF_PC_JACOBI = 1, UF_PC_AI1 = 2, UF_PC_AI2 = 3, UF_PC_MG = 4 };
 /* Inflow profile: uniform speed, the log-law of Sec. 5.1, or a table. */
 enum { UF_INFLOW_UNIFORM = 0, UF_INFLOW_LOGLAW = 1, UF_INFLOW_PROFILE = 2 };
@@ -496,7 +501,8 @@ uf_status uf_adjoint_step_at(uf_grid g, const void* const* state_n_dev, const vo
 enum { UF_TK_CG_AD = 0, UF_TK_CG_AXPY = 1, UF_TK_CG_PRECOND = 2, UF_TK_MG_DOWN0 = 3, UF_TK_MG_UP0 = 4,
        UF_TK_MG_COARSE = 5, UF_TK_CG_INIT = 6, UF_TK_ADVECT_FWD = 7, UF_TK_ADVECT_CORR = 8,
        UF_TK_DIFFUSE = 9, UF_TK_DRAG = 10, UF_TK_PROJECT = 11, UF_TK_TURB = 12, UF_TK_MG_UPDATE0 = 13,
-       UF_TK_MG_RUPD0 = 14, UF_TK_COUNT = 15 };
+       UF_TK_MG_RUPD0 = 14, UF_TK_DS_ROW = 15, UF_TK_DS_COL = 16, UF_TK_DS_TRI = 17, UF_TK_DS_FINISH = 18,
+       UF_TK_COUNT = 19 };
 uf_status uf_kernel_timer_enable(uf_grid g, uint32_t mask);
 uf_status uf_kernel_timer_read(uf_grid g, int32_t kernel, double* total_ms, int64_t* launches);
 

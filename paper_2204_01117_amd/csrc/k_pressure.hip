@@ -124,8 +124,35 @@ __device__ __forceinline__ T diag_x(const Params<T>& P, int i) {
   return ((i > 0 || P.bc[0] == OUTLET) ? P.ih2[0] : T(0)) + ((i < P.L.nx - 1 || P.bc[1] == OUTLET) ? P.ih2[0] : T(0));
 }
 
+// div u* of one cell after another along x at fixed (j, k).  A cell at an
+// inlet takes the inflow itself as its outer face, not the face's rounded
+// copy: the rounding of the mean inflow is a flux that every cell up to the
+// outlet carries, and turned up as a pressure error growing along the
+// domain (256x256x64 in FP32: 1.6e-6 of the pressure).
+template <class T>
+struct CellDiv {
+  T yz, x0, x1;   // what the inflow's remainder adds: y sides, first and last cell along x
+  __device__ __forceinline__ CellDiv(const Params<T>& P, int j, int k) {
+    const T lu = inflow_rest(P, 0, k) * P.ih[0], lv = inflow_rest(P, 1, k) * P.ih[1];
+    yz = (j == P.L.ny - 1 && P.bc[3] == INLET ? lv : T(0)) - (j == 0 && P.bc[2] == INLET ? lv : T(0));
+    x0 = P.bc[0] == INLET ? -lu : T(0);
+    x1 = P.bc[1] == INLET ? lu : T(0);
+  }
+  __device__ __forceinline__ T at(const Params<T>& P, const T* __restrict__ U, const T* __restrict__ V,
+                                  const T* __restrict__ W, long long o, int i) const {
+    const Layout& L = P.L;
+    const T rest = yz + (i == 0 ? x0 : T(0)) + (i == L.nx - 1 ? x1 : T(0));
+    return (U[o + L.SX] - U[o]) * P.ih[0] + (V[o + L.PZ] - V[o]) * P.ih[1] + (W[o + 1] - W[o]) * P.ih[2] + rest;
+  }
+};
+
 // r = b - A x with b = -(rho/dt) div u* (or a given b); partials of ||b||^2
-// and ||r||^2.
+// and ||r||^2.  A x is formed from the differences to the neighbours (a
+// Neumann side's neighbour is the cell itself), which for a smooth x are
+// far smaller than x and round accordingly: with D x minus the neighbours'
+// sum, the rounding relative to x itself, turned into an error of the
+// smooth modes by A^-1, was the largest part of the FP32 pressure's error
+// (512x512x128: 1.5e-6 to 7e-6 of the pressure).
 template <class T>
 __global__ __launch_bounds__(kCgBlock) void k_cg_init(Params<T> P, const T* __restrict__ U, const T* __restrict__ V,
                                                       const T* __restrict__ W, const T* __restrict__ bin,
@@ -134,21 +161,17 @@ __global__ __launch_bounds__(kCgBlock) void k_cg_init(Params<T> P, const T* __re
   UF_CG_RANGE(L, ilen);
   double v[2] = {0.0, 0.0};
   if (i0 < i1) {
-    const T dyz = diag_yz(P, j, k);
+    const long long ym = j == 0 && P.bc[2] != OUTLET ? 0 : -L.PZ, yp = j == L.ny - 1 && P.bc[3] != OUTLET ? 0 : L.PZ;
+    const long long zm = k == 0 && P.bc[4] != OUTLET ? 0 : -1, zp = k == L.nz - 1 && P.bc[5] != OUTLET ? 0 : 1;
+    const CellDiv<T> div(P, j, k);
     long long o = L.at(i0, j, k);
     T xm = X[o - L.SX], xc = X[o];
     for (int i = i0; i < i1; ++i, o += L.SX) {
       const T xp = X[o + L.SX];
-      T b;
-      if (bin) {
-        b = bin[o];
-      } else {
-        const T div = (U[o + L.SX] - U[o]) * P.ih[0] + (V[o + L.PZ] - V[o]) * P.ih[1] + (W[o + 1] - W[o]) * P.ih[2];
-        b = -P.rho_dt * div;
-      }
-      const T ax = (dyz + diag_x(P, i)) * xc - (xp + xm) * P.ih2[0] - (X[o + L.PZ] + X[o - L.PZ]) * P.ih2[1] -
-                   (X[o + 1] + X[o - 1]) * P.ih2[2];
-      const T r = b - ax;
+      const T b = bin ? bin[o] : -P.rho_dt * div.at(P, U, V, W, o, i);
+      const T wm = i == 0 && P.bc[0] != OUTLET ? T(0) : P.ih2[0], wp = i == L.nx - 1 && P.bc[1] != OUTLET ? T(0) : P.ih2[0];
+      const T r = b + (wm * (xm - xc) + wp * (xp - xc) + P.ih2[1] * ((X[o + yp] - xc) + (X[o + ym] - xc)) +
+                       P.ih2[2] * ((X[o + zp] - xc) + (X[o + zm] - xc)));
       R[o] = r;
       v[0] += (double)b * (double)b;
       v[1] += (double)r * (double)r;
@@ -198,16 +221,10 @@ __global__ __launch_bounds__(kCgBlock) void k_cg_restart(Params<T> P, const T* _
   if (!c.st->restart) return;
   const Layout& L = P.L;
   UF_CG_RANGE(L, ilen);
+  const CellDiv<T> div(P, j, k);
   for (int i = i0; i < i1; ++i) {
     const long long o = L.at(i, j, k);
-    T b;
-    if (bin) {
-      b = bin[o];
-    } else {
-      const T div = (U[o + L.SX] - U[o]) * P.ih[0] + (V[o + L.PZ] - V[o]) * P.ih[1] + (W[o + 1] - W[o]) * P.ih[2];
-      b = -P.rho_dt * div;
-    }
-    R[o] = b;
+    R[o] = bin ? bin[o] : -P.rho_dt * div.at(P, U, V, W, o, i);
     X[o] = T(0);
   }
 }

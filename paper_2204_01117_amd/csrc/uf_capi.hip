@@ -283,6 +283,7 @@ void free_grid(Grid* g) {
   for (hipEvent_t e : g->timer_pool) (void)hipEventDestroy(e);
   g->timer_pool.clear();
   mg_free(*g);
+  direct_free(*g);
 }
 
 // Copy the CG status to the host behind the work enqueued so far; the host
@@ -302,6 +303,24 @@ struct SolveResult {
   bool first_final = false;   // the first chunk's status already ended the solve
 };
 
+// The start of a solve: r0 = b - A x0, the stopping threshold and, for the
+// CG, the first preconditioner application.
+template <class T>
+void enqueue_start(Grid& g, const Params<T>& P, void* const Qs[3], const void* b) {
+  launch_cg_start<T>(g, P, Qs, b);
+  if (!g.direct) launch_cg_precond<T>(g, P, 0);
+}
+
+// Iterations t .. t + m - 1 of a solve and its status after them.
+template <class T>
+void enqueue_iterations(Grid& g, const Params<T>& P, int t, int m) {
+  for (int q = 0; q < m; ++q) {
+    if (g.direct) launch_direct_iteration<T>(g, P, t + q);
+    else launch_cg_iteration<T>(g, P, t + q);
+  }
+  if (!g.direct) launch_cg_status(g, t + m);   // each direct iteration ends with its status
+}
+
 // Pressure solve: r0 = b - A x0 and the stopping threshold, the first
 // preconditioner application, then iterations enqueued in chunks with the
 // device status read after each chunk.  The first chunk is as long as the
@@ -311,11 +330,12 @@ template <class T>
 void solve_chunk(Grid& g, const Params<T>& P) {
   const int maxit = g.cfg.cg_maxit;
   int t = g.cg_t;
-  int m = t == 0 ? (g.last_iters > 0 ? g.last_iters : 4) : std::max(1, t / 8);
+  // direct iterations are few and reduce the residual by orders of magnitude each
+  int m = t == 0 ? (g.last_iters > 0 ? g.last_iters : (g.direct ? 1 : 4)) : (g.direct ? 1 : std::max(1, t / 8));
   if (t + m > maxit) m = maxit - t;
   if (m < 1) m = 1;
-  for (int q = 0; q < m; ++q, ++t) launch_cg_iteration<T>(g, P, t);
-  launch_cg_status(g, t);
+  enqueue_iterations<T>(g, P, t, m);
+  t += m;
   check_launch();
   post_status(g);
   g.cg_t = t;
@@ -324,8 +344,7 @@ void solve_chunk(Grid& g, const Params<T>& P) {
 // Enqueue the start of a solve and its first chunk (no host wait).
 template <class T>
 void solve_begin(Grid& g, const Params<T>& P, void* const Qs[3], const void* b) {
-  launch_cg_start<T>(g, P, Qs, b);
-  launch_cg_precond<T>(g, P, 0);
+  enqueue_start<T>(g, P, Qs, b);
   check_launch();
   g.cg_t = 0;
   solve_chunk<T>(g, P);
@@ -498,7 +517,7 @@ template <class T>
 void upload_inflow(Grid& g) {
   const uf_config& c = g.cfg;
   const int nz = c.nz;
-  std::vector<T> tab(2 * (nz + 2));
+  std::vector<T> tab(4 * (nz + 2));
   const double th = c.wind_dir_deg * (M_PI / 180.0);
   const double dir[2] = {std::cos(th), std::sin(th)};
   for (int k = -1; k <= nz; ++k) {
@@ -514,8 +533,11 @@ void upload_inflow(Grid& g) {
       const int kk = k < 0 ? 0 : (k > nz - 1 ? nz - 1 : k);
       s = g.profile[kk];
     }
-    tab[0 * (nz + 2) + (k + 1)] = T(s * dir[0]);
-    tab[1 * (nz + 2) + (k + 1)] = T(s * dir[1]);
+    for (int q = 0; q < 2; ++q) {
+      const T v = T(s * dir[q]);
+      tab[q * (nz + 2) + (k + 1)] = v;
+      tab[(2 + q) * (nz + 2) + (k + 1)] = T(s * dir[q] - (double)v);
+    }
   }
   upload(g, g.inflow, tab.data(), tab.size() * sizeof(T));
 }
@@ -538,11 +560,23 @@ int64_t extent(const uf_config* c, int32_t f, int32_t d[3]) {
   return (int64_t)e[0] * e[1] * e[2];
 }
 
+// The second solve stream, for grids whose CG iterations use it.  Only they
+// get one: every stream takes one of the process's few hardware queues, and
+// a batch of grids with idle second streams left fewer queues to its case
+// streams.
+void make_xstream(Grid& g) {
+  if (g.xstream || !mg_splits_update(g)) return;
+  UF_HIP_CHECK(hipStreamCreateWithFlags(&g.xstream, hipStreamNonBlocking));
+  UF_HIP_CHECK(hipEventCreate(&g.ev_xfork));   // completed inside a dispatch (hipExtLaunchKernel)
+  UF_HIP_CHECK(hipEventCreateWithFlags(&g.ev_xjoin, hipEventDisableTiming));
+}
+
 // Reverse of one step (see uf_adjoint_step).  The forward stages before
 // the projection are recomputed from the given state into the adjoint
 // workspace; then each enabled stage is reversed, last first.
 void adjoint_alloc(Grid& g) {
   if (g.XA) return;
+  make_xstream(g);
   const size_t bytes = g.nelem * g.esize;
   for (auto& set : g.AS)
     for (auto& q : set) q = galloc(g, bytes);
@@ -560,7 +594,7 @@ void adjoint_alloc(Grid& g) {
   g.Cbar = galloc(g, bytes);
   g.XA = galloc(g, bytes);
   UF_HIP_CHECK(hipMemsetAsync(g.XA, 0, bytes, g.stream));   // zero start and zero ghosts
-  const size_t tab = 2 * (size_t)(g.L.nz + 2) * g.esize;
+  const size_t tab = 4 * (size_t)(g.L.nz + 2) * g.esize;
   g.inflow0 = galloc(g, tab);
   UF_HIP_CHECK(hipMemsetAsync(g.inflow0, 0, tab, g.stream));
 }
@@ -582,6 +616,16 @@ struct PressureSwap {
     g.last_iters = saved_iters;
     std::swap(g.X, other);
   }
+};
+
+// The reverse step's own solve iterates with the CG: its result is a
+// gradient, held in FP64 for the porosity, that callers compare between
+// runs, and the CG's iterate differs from the direct one by the tolerance.
+struct IterativeSolve {
+  Grid& g;
+  const bool was;
+  explicit IterativeSolve(Grid& g_) : g(g_), was(g_.direct) { g.direct = false; }
+  ~IterativeSolve() { g.direct = was; }
 };
 
 // The eddy viscosity the recomputed diffusion reads (the state's own).
@@ -688,6 +732,7 @@ SolveResult adjoint_step(Grid& g, const void* const* state, const void* const* s
   SolveResult res;
   if (st & UF_STAGE_PROJECT) {
     PressureSwap ps(g, g.XA, g.adj_last_iters);
+    IterativeSolve it(g);
     res = solve_pressure<T>(g, P0, a, nullptr);
     launch_project<T>(g, P0, a, A1);
     a = A1;
@@ -795,6 +840,10 @@ struct Batch {
   hipGraphExec_t front = nullptr, back = nullptr;
   std::vector<hipGraphExec_t> solve;
 };
+
+// Iterations to capture for a case's solves: as many as its last solve took
+// (direct), or a couple more (CG: those past convergence return at once).
+int solve_cap(const Grid& g) { return g.direct ? std::max(1, g.last_iters) : std::max(4, g.last_iters + 2); }
 
 int stage_blocks(const BatchTune& t, int s, int total) {
   const int want = t.blocks[s] > 0 ? t.blocks[s] : total;
@@ -930,10 +979,8 @@ void capture_solve(Batch& b, size_t c) {
   Grid& g = *b.g[c];
   capture(b.cs[c], &b.solve[c], [&] {
     const Params<T> P = make_params<T>(g);
-    launch_cg_start<T>(g, P, g.Q[1], nullptr);
-    launch_cg_precond<T>(g, P, 0);
-    for (int t = 0; t < b.kcap[c]; ++t) launch_cg_iteration<T>(g, P, t);
-    launch_cg_status(g, b.kcap[c]);
+    enqueue_start<T>(g, P, g.Q[1], nullptr);
+    enqueue_iterations<T>(g, P, 0, b.kcap[c]);
     UF_HIP_CHECK(hipMemcpyAsync(g.st_host, g.st, sizeof(CgState), hipMemcpyDeviceToHost, b.cs[c]));
     join_x(g);
   });
@@ -1009,8 +1056,8 @@ void batch_steps(Batch& b, int nsteps, std::vector<StepAccum>& acc) {
       acc[c].nonfinite |= st.nonfinite;
       acc[c].nf_state |= st.nf_state;
       // a solve graph too short (or far too long) for this case is captured again
-      if (st.iter > b.kcap[c] || st.iter + 4 < b.kcap[c]) {
-        b.kcap[c] = std::min(g.cfg.cg_maxit, st.iter + 2);
+      if (st.iter > b.kcap[c] || st.iter + (g.direct ? 1 : 4) < b.kcap[c]) {
+        b.kcap[c] = std::min(g.cfg.cg_maxit, solve_cap(g));
         UF_HIP_CHECK(hipStreamSynchronize(b.cs[c]));
         drop_solve(b, c);
       }
@@ -1141,7 +1188,7 @@ uf_status uf_create_grid(const uf_config* cfg, uf_grid* out) {
       UF_HIP_CHECK(hipMemsetAsync(*q, 0, bytes, g->stream));
     }
     g->PHI = galloc(*g, (size_t)cfg->nx * cfg->ny * cfg->nz * g->esize);
-    g->inflow = galloc(*g, 2 * (cfg->nz + 2) * g->esize);
+    g->inflow = galloc(*g, 4 * (cfg->nz + 2) * g->esize);
     const CgLaunch cl = cg_launch(L);
     g->cg_nb = (size_t)cl.gx * cl.gy;
     g->cg_nb_rz = cfg->precond == UF_PC_MG ? mg_fine_blocks(L) : g->cg_nb;
@@ -1171,29 +1218,25 @@ uf_status uf_create_grid(const uf_config* cfg, uf_grid* out) {
     upload_inflow<float>(*g);
     fill_phi_one<float>(*g);
     if (cfg->precond == UF_PC_MG) mg_setup<float>(*g);
+    if (direct_use(*cfg, g->esize)) direct_setup<float>(*g);
   } else {
     upload_inflow<double>(*g);
     fill_phi_one<double>(*g);
     if (cfg->precond == UF_PC_MG) mg_setup<double>(*g);
+    if (direct_use(*cfg, g->esize)) direct_setup<double>(*g);
   }
   // partial-sum slots, sized for every kernel that writes them (the
   // multigrid hierarchy decides whether the level-0 restriction is one)
   {
+    g->direct = direct_use(*cfg, g->esize);
     const size_t fused = mg_fused_blocks(*g);
     g->mg_fused = fused > 0;
-    g->cg_nb_rr = std::max(g->cg_nb, fused);
+    g->cg_nb_rr = std::max(std::max(g->cg_nb, fused), g->direct ? direct_blocks(L) : 0);
     g->part_stride = std::max(std::max(g->cg_nb, g->cg_nb_rr), std::max(g->cg_nb_rz, g->cg_nb_dq));
     g->partials = (double*)galloc(*g, S_NSLOT_HOST * g->part_stride * sizeof(double));
     UF_HIP_CHECK(hipMemsetAsync(g->partials, 0, S_NSLOT_HOST * g->part_stride * sizeof(double), g->stream));
   }
-  if (mg_splits_update(*g)) {
-    // only grids whose iterations use it get the second stream: every
-    // stream takes one of the process's few hardware queues, and a batch of
-    // grids with idle second streams left fewer queues to its case streams
-    UF_HIP_CHECK(hipStreamCreateWithFlags(&g->xstream, hipStreamNonBlocking));
-    UF_HIP_CHECK(hipEventCreate(&g->ev_xfork));   // completed inside a dispatch (hipExtLaunchKernel)
-    UF_HIP_CHECK(hipEventCreateWithFlags(&g->ev_xjoin, hipEventDisableTiming));
-  }
+  if (!g->direct) make_xstream(*g);
   if (g->esize == 4) init_state<float>(*g);
   else init_state<double>(*g);
   UF_HIP_CHECK(hipStreamSynchronize(g->stream));
@@ -1752,7 +1795,7 @@ uf_status uf_batch_create(const uf_grid* grids, int32_t n, uf_batch* out) {
       b->tune.blocks[st] = 0;
       b->tune.ms[st] = 0.f;
     }
-    for (int i = 0; i < n; ++i) b->kcap.push_back(std::max(4, grids[i]->last_iters + 2));
+    for (int i = 0; i < n; ++i) b->kcap.push_back(std::min(grids[i]->cfg.cg_maxit, solve_cap(*grids[i])));
     UF_HIP_CHECK(hipMalloc(&b->kc_dev, sizeof(int) * n));
     UF_HIP_CHECK(hipHostMalloc(&b->kc_host, sizeof(int) * n, hipHostMallocDefault));
     if (b->esize == 4) build_table<float>(*b);

@@ -45,7 +45,8 @@ struct Params {
   T cap;            // nu_max - nu: upper bound of the eddy viscosity
   T k_in, w_in, k_min, w_min;
   T lim_coef;       // C_lim / sqrt(C_mu / 2): omega limiter per unit |S|
-  const T* inflow;  // [2][nz+2]: inflow u and v at vertical index k in [-1, nz]
+  const T* inflow;  // [2][nz+2]: inflow u and v at vertical index k in [-1, nz]; then
+                    // [2][nz+2]: what rounding to T took from them
 };
 
 // max/min that propagate NaN (like numpy.maximum/minimum), so that a
@@ -64,6 +65,12 @@ template <class T>
 __device__ __forceinline__ T inflow_comp(const Params<T>& P, int c, int k) {
   if (c == 2) return T(0);
   return P.inflow[c * (P.L.nz + 2) + (k + 1)];
+}
+
+// The inflow minus its value in T.
+template <class T>
+__device__ __forceinline__ T inflow_rest(const Params<T>& P, int c, int k) {
+  return P.inflow[(2 + c) * (P.L.nz + 2) + (k + 1)];
 }
 
 // Value of the ghost across side (a, hi) of component c, given the value v of

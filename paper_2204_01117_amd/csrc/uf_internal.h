@@ -108,7 +108,7 @@ struct Grid {
   void* NUT = nullptr;
   void* C = nullptr;         // drag coefficient per cell
   void* PHI = nullptr;       // porosity, compact nx*ny*nz
-  void* inflow = nullptr;    // [2][nz+2]
+  void* inflow = nullptr;    // [4][nz+2] (Params::inflow)
   // pressure solve
   void* X = nullptr;         // pressure (the CG iterate)
   void* R = nullptr;         // residual after an even number of updates
@@ -161,6 +161,12 @@ struct Grid {
   void* mg_cinv = nullptr;      // dense inverse of the coarsest operator
   void* mg_table = nullptr;     // device copy of the level descriptors
   double mg_omega = 0.8;        // Jacobi weight of the smoother
+  // direct pressure solve (k_direct.hip)
+  bool direct = false;          // this grid's solves are direct (off while the reverse step solves)
+  void* ds_y[2] = {};           // eigenvectors along y: [cell][mode], [mode][cell]
+  void* ds_z[2] = {};           // ... along z
+  void* ds_w[2] = {};           // the transformed residual (no ghosts: k_direct.hip's W layout)
+  double* ds_lam = nullptr;     // eigenvalues along y, then along z
   int last_iters = 0;
   int cg_t = 0;                 // CG iterations enqueued in the current solve
   // kernel timer (see uf_kernel_timer_enable)
@@ -256,6 +262,11 @@ size_t mg_fused_blocks(const Grid& g);
 bool mg_splits_update(const Grid& g);
 template <class T> void mg_apply(Grid& g, const Params<T>& P, const void* r, void* z);
 void mg_free(Grid& g);
+bool direct_use(const uf_config& c, size_t esize);
+size_t direct_blocks(const Layout& L);
+template <class T> void direct_setup(Grid& g);
+void direct_free(Grid& g);
+template <class T> void launch_direct_iteration(Grid& g, const Params<T>& P, int t);
 
 // Marks the one kernel launched (through launch_k) in its scope as kernel
 // id of the timer.
