@@ -90,10 +90,29 @@ __device__ __forceinline__ void ds_mul(const T* __restrict__ As, int sa, const T
   }
 }
 
+// The forward product over y sums the cells in their order; its rounding,
+// relative to the partial sums, is an error of every mode alike, which the
+// division by the eigenvalues turns into an error of the smooth modes (1e-6
+// of the FP32 pressure at 256x256x64).  In FP32 (SPLIT) it therefore sums
+// kDsChain slices (64 terms) at a time and those sums among themselves:
+// from about sqrt(K / 4) roundings to 4, and 3e-7 there.
+constexpr int kDsChain = 4;
+
+template <class T, int WM, int WN>
+__device__ __forceinline__ void ds_fold(typename Mfma<T>::Acc (&acc)[WM][WN], typename Mfma<T>::Acc (&tot)[WM][WN]) {
+#pragma unroll
+  for (int p = 0; p < WM; ++p)
+#pragma unroll
+    for (int q = 0; q < WN; ++q) {
+      tot[p][q] += acc[p][q];
+      acc[p][q] = typename Mfma<T>::Acc{};
+    }
+}
+
 // C[m][n] = sum_k At[k][m] B[k][n], m < M, n < N, k < K: the transform over
 // y.  At is padded with zeros to multiples of BK rows and 128 columns; B and
 // C have row stride ldw (a multiple of the vector width).
-template <class T, int WM, int WN>
+template <class T, int WM, int WN, bool SPLIT>
 __global__ __launch_bounds__(kDsThreads) void k_ds_col(const T* __restrict__ At, int lda, const T* __restrict__ B,
                                                        T* __restrict__ C, int M, int K, int N, long long ldw, int mt,
                                                        int nt, const CgState* __restrict__ st) {
@@ -136,15 +155,21 @@ __global__ __launch_bounds__(kDsThreads) void k_ds_col(const T* __restrict__ At,
     }
   };
   const int w = tid >> 6, wm = (w >> 1) * WM * X::MT, wn = (w & 1) * WN * X::MT;
-  typename X::Acc acc[WM][WN] = {};
+  typename X::Acc acc[WM][WN] = {}, tot[SPLIT ? WM : 1][SPLIT ? WN : 1] = {};
   load(0);
   store(0);
   __syncthreads();
-  int s = 0;
+  int s = 0, c = 0;
   for (int k0 = 0; k0 < K; k0 += D::BK, s ^= 1) {
     const bool more = k0 + D::BK < K;
     if (more) load(k0 + D::BK);
     ds_mul<T, WM, WN>(As[s], D::SM, Bs[s], D::SN, wm, wn, acc);
+    if constexpr (SPLIT) {
+      if (++c == kDsChain || !more) {
+        ds_fold<T, WM, WN>(acc, tot);
+        c = 0;
+      }
+    }
     if (more) store(s ^ 1);
     __syncthreads();
   }
@@ -158,7 +183,7 @@ __global__ __launch_bounds__(kDsThreads) void k_ds_col(const T* __restrict__ At,
 #pragma unroll
       for (int e = 0; e < X::NR; ++e) {
         const int m = m0 + wm + p * X::MT + X::row(e, hi);
-        if (m < M) C[m * ldw + n] = acc[p][q][e];
+        if (m < M) C[m * ldw + n] = SPLIT ? tot[SPLIT ? p : 0][SPLIT ? q : 0][e] : acc[p][q][e];
       }
     }
 }
@@ -624,10 +649,15 @@ bool direct_use(const uf_config& c, size_t esize) {
 
 static int up(int n, int m) { return (n + m - 1) / m * m; }
 
-// Eigenvalues (weight w) and orthonormal eigenvectors v[i * n + m] (mode m)
+// Eigenvalues (weight w) and orthonormal eigenvectors v[i * n + c] (column c)
 // of the one-dimensional operator on n cells with the given open (outlet)
 // sides: theta_m = m pi / n, (m + 1) pi / (n + 1) or (2m + 1) pi / (2n + 1).
-// The angles are multiples of one, so a table of sines covers them.
+// The angles are multiples of one, so a table of sines covers them.  Mode m
+// is column n - 1 - m: the products back sum the columns in order, and with
+// the smooth modes, which hold most of the solution, coming last the partial
+// sums stay small until the end, and so do their roundings (the residual an
+// FP32 iteration leaves: 256x256x64 4.4e-6 -> 6.0e-7 ||b||, 512x512x128
+// 4.9e-5 -> 4.0e-6; most steps then need one iteration instead of two).
 static void axis_modes(int n, double w, bool lo, bool hi, std::vector<double>& lam, std::vector<double>& v) {
   const long long q = (lo && hi) ? n + 1 : (lo || hi) ? 2 * n + 1 : n;   // theta_m = a_m pi / q
   // sines at multiples of pi / (2q)
@@ -639,13 +669,14 @@ static void axis_modes(int n, double w, bool lo, bool hi, std::vector<double>& l
   for (int m = 0; m < n; ++m) {
     const long long a = (lo && hi) ? m + 1 : (lo || hi) ? 2 * m + 1 : m;
     const double s = sine(a);   // sin(theta / 2)
-    lam[m] = 4.0 * w * s * s;
+    const int col = n - 1 - m;
+    lam[col] = 4.0 * w * s * s;
     const double norm = (lo && hi) ? std::sqrt(2.0 / (n + 1))
                                    : (lo || hi) ? 2.0 / std::sqrt(2.0 * n + 1.0) : std::sqrt((m ? 2.0 : 1.0) / n);
     for (int i = 0; i < n; ++i) {
       const long long cell = lo && !hi ? n - 1 - i : i;   // distance from the closed end
       // sin((i + 1) theta), or cos((cell + 1/2) theta) = sin(pi/2 + ...)
-      v[(size_t)i * n + m] = norm * ((lo && hi) ? sine(2 * (i + 1) * a) : sine((2 * cell + 1) * a + q));
+      v[(size_t)i * n + col] = norm * ((lo && hi) ? sine(2 * (i + 1) * a) : sine((2 * cell + 1) * a + q));
     }
   }
 }
@@ -701,7 +732,7 @@ static void launch_row(Grid& g, const T* in, T* out, const T* E, long long ldw) 
   else go(k_ds_row<T, 2, 1, FWD>, 4 * MT, 2 * MT);
 }
 
-template <class T>
+template <class T, bool FWD>
 static void launch_col(Grid& g, const T* E, const T* in, T* out, long long ldw) {
   const Layout& L = g.L;
   const int lda = up(L.ny, 128), N = L.nx * L.nz;
@@ -712,12 +743,17 @@ static void launch_col(Grid& g, const T* E, const T* in, T* out, long long ldw) 
              (const CgState*)g.st);
   };
   constexpr int MT = Mfma<T>::MT;
+  constexpr bool SPLIT = FWD && sizeof(T) == 4;
   // the large tile halves the LDS traffic per product; the small one wastes
   // less on a ragged ny and gives short axes enough blocks
-  if ((long long)up(L.ny, 4 * MT) * 8 <= (long long)L.ny * 9 && (long long)L.ny * N >= 1024LL * 16 * MT * MT)
-    go(k_ds_col<T, 2, 2>, 4 * MT, 4 * MT);
-  else
-    go(k_ds_col<T, 1, 1>, 2 * MT, 2 * MT);
+  if ((long long)up(L.ny, 4 * MT) * 8 <= (long long)L.ny * 9 && (long long)L.ny * N >= 1024LL * 16 * MT * MT) {
+    // with a second set of sums the widest tile leaves two wavefronts per
+    // SIMD: 368 us at 512x512x128 against 352 with half of it (299 and 310
+    // with one set)
+    if (SPLIT) go(k_ds_col<T, 2, 1, SPLIT>, 4 * MT, 2 * MT);
+    else go(k_ds_col<T, 2, 2, SPLIT>, 4 * MT, 4 * MT);
+  } else
+    go(k_ds_col<T, 1, 1, SPLIT>, 2 * MT, 2 * MT);
 }
 
 template <class T, int LC>
@@ -752,13 +788,13 @@ void launch_direct_iteration(Grid& g, const Params<T>& P, int t) {
   T* W1 = (T*)g.ds_w[1];
   if (t > 0) launch_finish<true, T>(g, P, resid(g, t - 1), resid(g, t));
   launch_row<T, true>(g, (const T*)resid(g, t), W0, (const T*)g.ds_z[0], ldw);
-  launch_col<T>(g, (const T*)g.ds_y[0], W0, W1, ldw);
+  launch_col<T, true>(g, (const T*)g.ds_y[0], W0, W1, ldw);
   switch (ds_chunk(L.nx)) {
     case 8: launch_tri<T, 8>(g, W1, ldw); break;
     case 16: launch_tri<T, 16>(g, W1, ldw); break;
     default: launch_tri<T, 32>(g, W1, ldw); break;
   }
-  launch_col<T>(g, (const T*)g.ds_y[1], W1, W0, ldw);
+  launch_col<T, false>(g, (const T*)g.ds_y[1], W1, W0, ldw);
   launch_row<T, false>(g, W0, (T*)g.Z, (const T*)g.ds_z[1], ldw);
   launch_finish<false, T>(g, P, resid(g, t), nullptr);
   hipLaunchKernelGGL(k_ds_status, dim3(1), dim3(256), 0, g.stream, make_ctl(g), t + 1);
