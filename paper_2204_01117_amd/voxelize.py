@@ -50,17 +50,13 @@ def voxelize(n, h, verts, tris, tri_begin, phi_obj, sub=4, dtype="f32", device="
 
 def _smooth_objects(n, h, boxes, cylinders, width):
     """uf_smooth_objects and the host arrays it points to."""
-    bx = [float(v) for row in boxes for v in row]
-    cy = [float(v) for row in cylinders for v in row]
-    bk = (ctypes.c_double * max(len(bx), 1))(*bx)
-    ck = (ctypes.c_double * max(len(cy), 1))(*cy)
+    bk, ck = (np.array(rows, dtype=np.float64).ravel() for rows in (boxes, cylinders))
     o = L.uf_smooth_objects()
     o.nx, o.ny, o.nz = (int(x) for x in n)
     o.dx, o.dy, o.dz = (float(x) for x in h)
     o.width = float(width)
     o.nboxes, o.ncyls = len(boxes), len(cylinders)
-    o.boxes = ctypes.cast(bk, ctypes.POINTER(ctypes.c_double))
-    o.cylinders = ctypes.cast(ck, ctypes.POINTER(ctypes.c_double))
+    o.boxes, o.cylinders = (a.ctypes.data_as(ctypes.POINTER(ctypes.c_double)) for a in (bk, ck))
     return o, (bk, ck)
 
 
