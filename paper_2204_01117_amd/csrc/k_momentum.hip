@@ -265,16 +265,7 @@ __global__ __launch_bounds__(kFaceBlock) void k_project(Params<T> P, const T* __
   project_faces(P, U, V, W, Pp, Uo, Vo, Wo, bx, ib);
 }
 
-// ------------------------------------------------ boundary refresh (in place)
-template <int C, class T>
-__global__ __launch_bounds__(kFaceBlock) void k_face_bc(Params<T> P, T* __restrict__ q) {
-  UF_FACE_THREAD(P.L);
-  if (!owns_face<C, T>(P.L, i, j, k)) return;
-  T val;
-  if (!face_dirichlet<C>(P, i, j, k, &val)) val = q[P.L.at(i, j, k)];
-  store_face<C>(q, P, i, j, k, val);
-}
-
+// ------------------------------------------------------------ initial state
 // Initial state: the inflow profile on every face (fixed faces keep their
 // boundary value).
 template <int C, class T>
@@ -402,14 +393,6 @@ void launch_project(Grid& g, const Params<T>& P, void* const Qin[3], void* const
 }
 
 template <class T>
-void launch_face_bc(Grid& g, const Params<T>& P, void* q, int comp) {
-  const dim3 grid = face_grid(P.L);
-  if (comp == 0) hipLaunchKernelGGL((k_face_bc<0, T>), grid, dim3(kFaceBlock), 0, g.stream, P, (T*)q);
-  if (comp == 1) hipLaunchKernelGGL((k_face_bc<1, T>), grid, dim3(kFaceBlock), 0, g.stream, P, (T*)q);
-  if (comp == 2) hipLaunchKernelGGL((k_face_bc<2, T>), grid, dim3(kFaceBlock), 0, g.stream, P, (T*)q);
-}
-
-template <class T>
 void launch_face_init(Grid& g, const Params<T>& P, void* const Q[3]) {
   const dim3 grid = face_grid(P.L);
   hipLaunchKernelGGL((k_face_init<0, T>), grid, dim3(kFaceBlock), 0, g.stream, P, (T*)Q[0]);
@@ -422,7 +405,6 @@ void launch_face_init(Grid& g, const Params<T>& P, void* const Q[3]) {
   template void launch_diffuse<T>(Grid&, const Params<T>&, void* const[3], void* const[3]);          \
   template void launch_drag<T>(Grid&, const Params<T>&, void* const[3], void* const[3]);             \
   template void launch_project<T>(Grid&, const Params<T>&, void* const[3], void* const[3], const int*); \
-  template void launch_face_bc<T>(Grid&, const Params<T>&, void*, int);                             \
   template void launch_face_init<T>(Grid&, const Params<T>&, void* const[3]);                      \
   template void launch_faces_multi<T>(int, const MultiCase<T>*, const CaseStarts&, int, int, int, int, int, hipStream_t);
 UF_INST(float)

@@ -654,16 +654,12 @@ SolveResult adjoint_step(Grid& g, const void* const* state, const void* const* s
   };
   // forward recompute, as in step_begin / step_end
   for (int c = 0; c < 3; ++c) {
-    launch_pack<T>(g, P, state[c], g.AS[0][c], c, 1);
-    launch_face_bc<T>(g, P, g.AS[0][c], c);
+    launch_put<T>(g, P, state[c], g.AS[0][c], c);
   }
   if (turb) {
-    launch_pack<T>(g, P, state[3], g.AT[AT_K], UF_K, 1);
-    launch_cell_bc<T>(g, P, g.AT[AT_K], 1, g.k_in);
-    launch_pack<T>(g, P, state[4], g.AT[AT_W], UF_OMEGA, 1);
-    launch_cell_bc<T>(g, P, g.AT[AT_W], 1, g.w_in);
-    launch_pack<T>(g, P, state[5], g.AT[AT_NUT], UF_NUT, 1);
-    launch_cell_bc<T>(g, P, g.AT[AT_NUT], 0, 0.0);
+    launch_put<T>(g, P, state[3], g.AT[AT_K], UF_K);
+    launch_put<T>(g, P, state[4], g.AT[AT_W], UF_OMEGA);
+    launch_put<T>(g, P, state[5], g.AT[AT_NUT], UF_NUT);
   }
   void* const* x = g.AS[0];
   if (st & UF_STAGE_ADVECT) {
@@ -685,8 +681,7 @@ SolveResult adjoint_step(Grid& g, const void* const* state, const void* const* s
   SolveResult fres;
   if (turb && state_next) {   // u^{n+1} given: the turbulence reverse linearises there
     for (int c = 0; c < 3; ++c) {
-      launch_pack<T>(g, P, state_next[c], g.AU[1][c], c, 1);
-      launch_face_bc<T>(g, P, g.AU[1][c], c);
+      launch_put<T>(g, P, state_next[c], g.AU[1][c], c);
     }
     unew = g.AU[1];
   } else if (turb) {   // recompute u^{n+1}
@@ -1406,16 +1401,11 @@ uf_status uf_set_field(uf_grid g, int32_t field, const void* src) {
       case UF_OMEGA: dst = g->Wo[g->kcur]; break;
       case UF_NUT: dst = g->NUT; break;
     }
-    launch_pack<T>(*g, P, src, dst, field, 1);
-    if (field <= UF_W) launch_face_bc<T>(*g, P, dst, field);
-    else if (field == UF_K) launch_cell_bc<T>(*g, P, dst, 1, g->k_in);
-    else if (field == UF_OMEGA) launch_cell_bc<T>(*g, P, dst, 1, g->w_in);
-    else if (field == UF_NUT) launch_cell_bc<T>(*g, P, dst, 0, 0.0);
+    launch_put<T>(*g, P, src, dst, field, nf_word(*g));
   };
   if (g->esize == 4) go(float());
   else go(double());
   check_launch();
-  UF_HIP_CHECK(hipMemsetAsync(nf_word(*g), 0, sizeof(int), g->stream));
   return UF_OK;
   UF_GUARD_END
 }

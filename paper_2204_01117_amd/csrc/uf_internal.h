@@ -209,11 +209,9 @@ template <class T> void launch_advect(Grid& g, const Params<T>& P, void* const Q
 template <class T> void launch_diffuse(Grid& g, const Params<T>& P, void* const Qin[3], void* const Qout[3]);
 template <class T> void launch_drag(Grid& g, const Params<T>& P, void* const Qin[3], void* const Qout[3]);
 template <class T> void launch_project(Grid& g, const Params<T>& P, void* const Qin[3], void* const Qout[3], const int* gate = nullptr);
-template <class T> void launch_face_bc(Grid& g, const Params<T>& P, void* q, int comp);
 template <class T> void launch_turb(Grid& g, const Params<T>& P, void* const Q[3], const void* K0, const void* W0, void* K1, void* W1, void* NUT, int update_kw, const int* gate = nullptr);
 // device word the drag and k-omega kernels set on a non-finite output
 inline int* nf_word(Grid& g) { return &g.st->nf_state; }
-template <class T> void launch_cell_bc(Grid& g, const Params<T>& P, void* q, int use_inlet, double inlet_value);
 // batched launches (one persistent launch for every case of a batch)
 template <class T>
 void launch_faces_multi(int stage, const MultiCase<T>* mc, const CaseStarts& cs, int band, int blocks, int sin,
@@ -223,6 +221,9 @@ void launch_turb_multi(const MultiCase<T>* mc, const CaseStarts& cs, int band, i
                        int nut_set, hipStream_t stream);
 int cell_queue_blocks(const Layout& L);
 template <class T> void launch_porosity(Grid& g, const Params<T>& P, const void* phi);
+// A compact field into padded storage with its boundary rules (launch_pack:
+// the values alone, or back out); nf, when given, is cleared.
+template <class T> void launch_put(Grid& g, const Params<T>& P, const void* src, void* dst, int field, int* nf = nullptr);
 template <class T> void launch_pack(Grid& g, const Params<T>& P, const void* src_padded, void* dst, int field, int unpack);
 template <class T> void launch_check_range(Grid& g, const void* phi, size_t n);
 // pressure solve
