@@ -12,8 +12,9 @@
 //      to the iterate and sums the residual that is left.
 //
 // That is one iteration; the solve stops, as the CG does, on
-// ||r|| <= tol ||b|| of the recursively updated residual.  FP32 steps from a
-// warm start need one, cold starts two.  The products cost 4 (ny + nz) flops
+// ||r|| <= tol ||b|| of the recursively updated residual.  Most FP32 steps
+// need one; where a large grid's first leaves a few times the threshold, the
+// next is two more sweeps instead of products (k_ds_finish, SMOOTH).  The products cost 4 (ny + nz) flops
 // per cell and iteration (FP32 on the matrix cores: 157 TFLOP/s nominal),
 // a CG iteration moves about 55 bytes per cell: see direct_use for where
 // the line between the two lies.
@@ -31,6 +32,11 @@ namespace uf {
 
 constexpr int kDsThreads = 256;
 constexpr double kDsOmega = 0.75;   // Jacobi weight of the closing sweep (0.7 to 0.85: within 10%)
+// Weights of the two sweeps of a smoothing iteration, and the multiple of the
+// threshold that it is trusted to remove: 5.3 to 5.8 of white noise, 3.3 to
+// 4.7 measured on grids of 17x33x31 to 512x6x8 cells, whose noise is smoother;
+// where it falls short a third iteration, of products, follows.
+constexpr double kDsOmegaZ = 0.563, kDsOmegaE = 1.485, kDsReach = 4.5;
 
 // Matrix-core tile of a type: MT x MT results, KT terms per instruction.
 // Lane l supplies A[l % MT][l / MT] and B[l / MT][l % MT] and holds column
@@ -109,6 +115,9 @@ __device__ __forceinline__ void ds_fold(typename Mfma<T>::Acc (&acc)[WM][WN], ty
     }
 }
 
+// Is there nothing for the transforms of the iteration to do?
+__device__ __forceinline__ bool ds_idle(const CgState* st) { return st->done || st->smooth; }
+
 // C[m][n] = sum_k At[k][m] B[k][n], m < M, n < N, k < K: the transform over
 // y.  At is padded with zeros to multiples of BK rows and 128 columns; B and
 // C have row stride ldw (a multiple of the vector width).
@@ -121,7 +130,7 @@ __global__ __launch_bounds__(kDsThreads) void k_ds_col(const T* __restrict__ At,
   using Vec = typename X::Vec;
   __shared__ __align__(16) T As[2][D::BK * D::SM];
   __shared__ __align__(16) T Bs[2][D::BK * D::SN];
-  if (st->done) return;   // uniform over the grid
+  if (ds_idle(st)) return;   // uniform over the grid
   int bm, bn;
   if (!xcd_block(mt, nt, bm, bn)) return;   // the tiles of one column of B run together
   const int tid = threadIdx.x, m0 = bm * D::BM, n0 = bn * D::BN;
@@ -203,7 +212,7 @@ __global__ __launch_bounds__(kDsThreads) void k_ds_row(Layout L, const T* __rest
   constexpr int SA = D::BM + 36;   // transposing stores of 16 (k) x 4 (rows) lanes hit distinct banks
   __shared__ __align__(16) T As[2][D::BK * SA];
   __shared__ __align__(16) T Bs[2][D::BK * D::SN];
-  if (st->done) return;
+  if (ds_idle(st)) return;
   int bn, bm;
   if (!xcd_block(nt, mt, bn, bm)) return;
   const int nz = L.nz, M = L.nx * L.ny;
@@ -300,7 +309,7 @@ __global__ __launch_bounds__(1024) void k_ds_tri(T* __restrict__ W, int n, int n
                                                  const double* __restrict__ lamz, int open_lo, int open_hi,
                                                  const CgState* __restrict__ st) {
   __shared__ double shy[16][64], shx[16][64], shn[64];
-  if (st->done) return;
+  if (ds_idle(st)) return;
   const int lane = threadIdx.x & 63, c = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nc = blockDim.x >> 6;
   const int line = blockIdx.x * 64 + lane, ln = min(line, nlines - 1);
   const int j = ln / nz, k = ln - j * nz, s = c * LC;
@@ -375,6 +384,14 @@ __global__ __launch_bounds__(1024) void k_ds_tri(T* __restrict__ W, int n, int n
 // in FP32, bound by HBM and the latency of its per-plane steps.
 // RESID: writes r1 - A e (the residual the next iteration starts from)
 // instead of touching x.
+// SMOOTH: an iteration of two sweeps alone, z = om_z D^-1 r in place of the
+// products' (made from r as it is read), e with a weight of its own.  The
+// residual that the products leave is rounding noise, about white in x, and
+// after the first sweep these two take it to 0.17 to 0.19 of its norm
+// whatever the ratio of the spacings (1 to 16 and to 1/16; the weights are
+// the minimax over those).  It costs a RESID and a SMOOTH pass, 127 + 134 us
+// at 512x512x128, against 1150 us for products (step 6.34 -> 5.43 ms), and
+// 36 + 46 against 270 us at 450x300x40.
 template <int FK_>
 struct DsFin {
   static constexpr int NTH = 512, FK = FK_, FJ = 1024 / FK_, NU = 2;   // NU columns per thread
@@ -406,19 +423,21 @@ __device__ __forceinline__ void ds_ring(int q, int b, int nj, int nk, int& j, in
 __device__ __forceinline__ int ds_clamp(int i, int n) { return min(max(i, -1), n + 1); }
 __device__ __forceinline__ int ds_class(int i, int n) { return (i <= 0 ? 1 : 0) | (i >= n - 1 ? 2 : 0); }
 
-template <int FK, bool RESID, class T>
+template <int FK, bool RESID, bool SMOOTH, class T>
 __global__ __launch_bounds__(512) void k_ds_finish(Params<T> P, const T* __restrict__ R, const T* __restrict__ Z,
-                                                   T* __restrict__ X, T* __restrict__ Rout, CgCtl c, T om, int nfi,
-                                                   int njt, int nkt) {
+                                                   T* __restrict__ X, T* __restrict__ Rout, CgCtl c, int nfi, int njt,
+                                                   int nkt) {
   using F = DsFin<FK>;
   __shared__ T sz[3][F::ZJ * F::ZK];
   __shared__ T se[2][F::EJ * F::EK];
   __shared__ T tab_d[64];
   __shared__ T tab_omd[64];
+  __shared__ T tab_z[SMOOTH ? 64 : 1];
   const CgState* st = c.st;
   const Layout& L = P.L;
-  if (st->done) {
-    if (RESID || !st->zero_rhs) return;   // uniform over the grid
+  // uniform over the grid
+  if (RESID ? (st->done || st->smoothed != (int)SMOOTH) : SMOOTH ? (st->done || !st->smooth) : ds_idle(st)) {
+    if (RESID || SMOOTH || !st->zero_rhs) return;
   }
   int bt, ch;
   if (!xcd_block(njt * nkt, (L.nx + nfi - 1) / nfi, bt, ch)) return;
@@ -426,7 +445,7 @@ __global__ __launch_bounds__(512) void k_ds_finish(Params<T> P, const T* __restr
   const int tid = threadIdx.x, kk = tid % F::FK, jr = tid / F::FK;
   const int j0 = (bt / nkt) * F::FJ, k0 = (bt % nkt) * F::FK;
   const int i0 = ch * nfi, i1 = min(L.nx, i0 + nfi);
-  if (!RESID && st->done) {   // b = 0: the solution is x = 0
+  if (!RESID && !SMOOTH && st->done) {   // b = 0: the solution is x = 0
     for (int u = 0; u < F::NU; ++u) {
       const int j = j0 + jr + F::ROWS * u, k = k0 + kk;
       if (j < L.ny && k < L.nz)
@@ -441,11 +460,12 @@ __global__ __launch_bounds__(512) void k_ds_finish(Params<T> P, const T* __restr
     };
     const T D = side(cx, 0) + side(cy, 1) + side(cz, 2);
     tab_d[tid] = D;
-    tab_omd[tid] = D > T(0) ? om / D : T(0);
+    tab_omd[tid] = D > T(0) ? T(SMOOTH ? kDsOmegaE : kDsOmega) / D : T(0);
+    if (SMOOTH) tab_z[tid] = D > T(0) ? T(kDsOmegaZ) / D : T(0);
   }
   // own columns (u < NU), then ring entries of the z plane and of the e plane
   long long oo[F::NU], zo[F::VZ], ro[F::VE];
-  int op[F::NU], oe[F::NU], ocl[F::NU], zp[F::VZ], ep[F::VE], eq[F::VE], ecl[F::VE];
+  int op[F::NU], oe[F::NU], ocl[F::NU], zp[F::VZ], zcl[F::VZ], ep[F::VE], eq[F::VE], ecl[F::VE];
   bool oin[F::NU], ein[F::VE];
   // A z is formed from differences to the neighbours (a Neumann side's
   // neighbour is the cell itself): for the smooth parts of z they are far
@@ -475,6 +495,7 @@ __global__ __launch_bounds__(512) void k_ds_finish(Params<T> P, const T* __restr
     if (q < F::ZRING) ds_ring(q, 2, F::FJ, F::FK, a, b);
     zp[v] = q < F::ZRING ? a * F::ZK + b : -1;
     zo[v] = (long long)(ds_clamp(j0 - 2 + a, L.ny) + 1) * L.PZ + (ds_clamp(k0 - 2 + b, L.nz) + 1);
+    zcl[v] = (ds_class(j0 - 2 + a, L.ny) << 2) | ds_class(k0 - 2 + b, L.nz);
   }
 #pragma unroll
   for (int v = 0; v < F::VE; ++v) {
@@ -495,11 +516,11 @@ __global__ __launch_bounds__(512) void k_ds_finish(Params<T> P, const T* __restr
     const long long bz = (long long)(ds_clamp(i, L.nx) + 1) * L.SX, br = (long long)(ds_clamp(i - 1, L.nx) + 1) * L.SX;
 #pragma unroll
     for (int u = 0; u < F::NU; ++u) {
-      zv[u] = Z[bz + oo[u]];
+      zv[u] = (SMOOTH ? R : Z)[bz + oo[u]];
       rv[u] = R[br + oo[u]];
     }
 #pragma unroll
-    for (int v = 0; v < F::VZ; ++v) zr[v] = Z[bz + zo[v]];
+    for (int v = 0; v < F::VZ; ++v) zr[v] = (SMOOTH ? R : Z)[bz + zo[v]];
 #pragma unroll
     for (int v = 0; v < F::VE; ++v) rr[v] = R[br + ro[v]];
     if (!RESID) {
@@ -515,9 +536,17 @@ __global__ __launch_bounds__(512) void k_ds_finish(Params<T> P, const T* __restr
   for (int u = 0; u < F::NU; ++u) z0[u] = z1[u] = z2[u] = e0[u] = e1[u] = e2[u] = q0[u] = q1[u] = T(0);
   double acc[1] = {0.0};
   load(i0 - 2);
+  if (SMOOTH) __syncthreads();   // tab_z
   for (int i = i0 - 2; i <= i1 + 1; ++i) {
     T* s2 = sz[(i + 6) % 3];
     T r1[F::NU], rg[F::VE], xo[F::NU];
+    if (SMOOTH) {
+      const int cz = ds_class(i, L.nx) << 4;
+#pragma unroll
+      for (int u = 0; u < F::NU; ++u) zv[u] *= tab_z[cz | ocl[u]];
+#pragma unroll
+      for (int v = 0; v < F::VZ; ++v) zr[v] *= tab_z[cz | zcl[v]];
+    }
 #pragma unroll
     for (int u = 0; u < F::NU; ++u) {
       z0[u] = z1[u];
@@ -602,6 +631,8 @@ __global__ __launch_bounds__(256) void k_ds_status(CgCtl c, int it) {
   const bool conv = rr <= st->tol2_bb;
   st->done = conv || st->nonfinite || it >= c.maxit;
   st->noconv = st->done && !conv && !st->nonfinite;
+  st->smoothed = st->smooth;
+  st->smooth = !st->smoothed && rr <= kDsReach * kDsReach * st->tol2_bb;
 }
 
 // ------------------------------------------------------------------- host
@@ -766,43 +797,52 @@ static void launch_tri(Grid& g, T* W, long long ldw) {
            g.bc[0] == OUTLET ? 1 : 0, g.bc[1] == OUTLET ? 1 : 0, (const CgState*)g.st);
 }
 
-template <bool RESID, class T>
+template <bool RESID, bool SMOOTH, class T>
 static void launch_finish(Grid& g, const Params<T>& P, const void* R, void* Rout) {
   const DsGeom d = ds_geom(P.L);
   TimedLaunch tl(g, UF_TK_DS_FINISH);
   auto go = [&](auto kernel) {
     launch_k(g, kernel, xcd_grid(d.njt * d.nkt, d.gy), dim3(512), P, (const T*)R, (const T*)g.Z, (T*)g.X, (T*)Rout,
-             make_ctl(g), T(kDsOmega), d.nfi, d.njt, d.nkt);
+             make_ctl(g), d.nfi, d.njt, d.nkt);
   };
-  if (d.fk == 64) go(k_ds_finish<64, RESID, T>);
-  else if (d.fk == 32) go(k_ds_finish<32, RESID, T>);
-  else go(k_ds_finish<16, RESID, T>);
+  if (d.fk == 64) go(k_ds_finish<64, RESID, SMOOTH, T>);
+  else if (d.fk == 32) go(k_ds_finish<32, RESID, SMOOTH, T>);
+  else go(k_ds_finish<16, RESID, SMOOTH, T>);
 }
 
 // Iteration t (from 0) of a direct solve; the residual is in resid(g, t).
+// After products that left little (CgState::smooth) it is a smoothing
+// iteration.  last: the status after iteration t - 1 when the host has it;
+// both kinds are enqueued otherwise, and one returns at once.
 template <class T>
-void launch_direct_iteration(Grid& g, const Params<T>& P, int t) {
+void launch_direct_iteration(Grid& g, const Params<T>& P, int t, const CgState* last) {
   const Layout& L = P.L;
   const long long ldw = up(L.nx * L.nz, 4);
   T* W0 = (T*)g.ds_w[0];
   T* W1 = (T*)g.ds_w[1];
-  if (t > 0) launch_finish<true, T>(g, P, resid(g, t - 1), resid(g, t));
-  launch_row<T, true>(g, (const T*)resid(g, t), W0, (const T*)g.ds_z[0], ldw);
-  launch_col<T, true>(g, (const T*)g.ds_y[0], W0, W1, ldw);
-  switch (ds_chunk(L.nx)) {
-    case 8: launch_tri<T, 8>(g, W1, ldw); break;
-    case 16: launch_tri<T, 16>(g, W1, ldw); break;
-    default: launch_tri<T, 32>(g, W1, ldw); break;
+  if (t > 0) {
+    if (!last || !last->smoothed) launch_finish<true, false, T>(g, P, resid(g, t - 1), resid(g, t));
+    if (last ? last->smoothed : t > 1) launch_finish<true, true, T>(g, P, resid(g, t - 1), resid(g, t));
+    if (!last || last->smooth) launch_finish<false, true, T>(g, P, resid(g, t), nullptr);
   }
-  launch_col<T, false>(g, (const T*)g.ds_y[1], W1, W0, ldw);
-  launch_row<T, false>(g, W0, (T*)g.Z, (const T*)g.ds_z[1], ldw);
-  launch_finish<false, T>(g, P, resid(g, t), nullptr);
+  if (t == 0 || !last || !last->smooth) {
+    launch_row<T, true>(g, (const T*)resid(g, t), W0, (const T*)g.ds_z[0], ldw);
+    launch_col<T, true>(g, (const T*)g.ds_y[0], W0, W1, ldw);
+    switch (ds_chunk(L.nx)) {
+      case 8: launch_tri<T, 8>(g, W1, ldw); break;
+      case 16: launch_tri<T, 16>(g, W1, ldw); break;
+      default: launch_tri<T, 32>(g, W1, ldw); break;
+    }
+    launch_col<T, false>(g, (const T*)g.ds_y[1], W1, W0, ldw);
+    launch_row<T, false>(g, W0, (T*)g.Z, (const T*)g.ds_z[1], ldw);
+    launch_finish<false, false, T>(g, P, resid(g, t), nullptr);
+  }
   hipLaunchKernelGGL(k_ds_status, dim3(1), dim3(256), 0, g.stream, make_ctl(g), t + 1);
 }
 
 template void direct_setup<float>(Grid&);
 template void direct_setup<double>(Grid&);
-template void launch_direct_iteration<float>(Grid&, const Params<float>&, int);
-template void launch_direct_iteration<double>(Grid&, const Params<double>&, int);
+template void launch_direct_iteration<float>(Grid&, const Params<float>&, int, const CgState*);
+template void launch_direct_iteration<double>(Grid&, const Params<double>&, int, const CgState*);
 
 }  // namespace uf

@@ -198,6 +198,7 @@ __global__ __launch_bounds__(256) void k_cg_start(CgCtl c, double tol) {
   const bool restart = isfinite(bb) && isfinite(rr) && rr > bb;
   if (restart) rr = bb;
   st->restart = restart;
+  st->smooth = st->smoothed = 0;
   st->bb = bb;
   st->rr = rr;
   st->iter = 0;

@@ -311,11 +311,12 @@ void enqueue_start(Grid& g, const Params<T>& P, void* const Qs[3], const void* b
   if (!g.direct) launch_cg_precond<T>(g, P, 0);
 }
 
-// Iterations t .. t + m - 1 of a solve and its status after them.
+// Iterations t .. t + m - 1 of a solve and its status after them; last is
+// the status before them when the host has read it.
 template <class T>
-void enqueue_iterations(Grid& g, const Params<T>& P, int t, int m) {
+void enqueue_iterations(Grid& g, const Params<T>& P, int t, int m, const CgState* last = nullptr) {
   for (int q = 0; q < m; ++q) {
-    if (g.direct) launch_direct_iteration<T>(g, P, t + q);
+    if (g.direct) launch_direct_iteration<T>(g, P, t + q, q == 0 ? last : nullptr);
     else launch_cg_iteration<T>(g, P, t + q);
   }
   if (!g.direct) launch_cg_status(g, t + m);   // each direct iteration ends with its status
@@ -334,7 +335,7 @@ void solve_chunk(Grid& g, const Params<T>& P) {
   int m = t == 0 ? (g.last_iters > 0 ? g.last_iters : (g.direct ? 1 : 4)) : (g.direct ? 1 : std::max(1, t / 8));
   if (t + m > maxit) m = maxit - t;
   if (m < 1) m = 1;
-  enqueue_iterations<T>(g, P, t, m);
+  enqueue_iterations<T>(g, P, t, m, t > 0 ? g.st_host : nullptr);   // t > 0: its status was waited for
   t += m;
   check_launch();
   post_status(g);

@@ -26,6 +26,8 @@ struct CgState {
   int maxit;
   int criterion;
   int nf_state;      // 1 once the drag or k-omega stage wrote a NaN/Inf (sticky; the solves leave it)
+  int smooth;        // direct solve: the next iteration only smooths (k_direct.hip)
+  int smoothed;      // and the last one did
   int restart;       // 1 when the initial guess was worse than zero and the solve started from x = 0
 };
 
@@ -267,7 +269,7 @@ bool direct_use(const uf_config& c, size_t esize);
 size_t direct_blocks(const Layout& L);
 template <class T> void direct_setup(Grid& g);
 void direct_free(Grid& g);
-template <class T> void launch_direct_iteration(Grid& g, const Params<T>& P, int t);
+template <class T> void launch_direct_iteration(Grid& g, const Params<T>& P, int t, const CgState* last);
 
 // Marks the one kernel launched (through launch_k) in its scope as kernel
 // id of the timer.

@@ -68,3 +68,21 @@ def test_direct_solve_from_a_guess_and_past_the_line_limit():
     assert st2["converged"] == 1 and rel(y, ref) <= 1e-10
     x, ref, st = solve((520, 6, 8), bc, "f64", 1e-13)
     assert st["converged"] == 1 and st["cg_iters"] > 4 and rel(x, ref) <= 1e-9
+
+
+@pytest.mark.parametrize("dtype,bound", [("f32", 1e-5), ("f64", 1e-10)])
+@pytest.mark.parametrize("shape,bc", CASES[2:])
+def test_direct_solve_smoothing_iteration(shape, bc, dtype, bound):
+    """A threshold just below what the first iteration leaves is met by an
+    iteration of sweeps (within 4.5 times it), one far below by products;
+    the iterate is then the solution to the same bounds."""
+    _, _, st = solve(shape, bc, dtype, 0.5)
+    assert st["cg_iters"] == 1
+    r0 = st["cg_rel_residual"]
+    for ratio in (2.0, 4.4, 20.0):
+        x, ref, st = solve(shape, bc, dtype, r0 / ratio)
+        print(shape, dtype, "ratio", ratio, "iterations", st["cg_iters"], "left", st["cg_rel_residual"] / r0,
+              flush=True)
+        assert st["converged"] == 1 and st["cg_rel_residual"] <= r0 / ratio
+        assert 2 <= st["cg_iters"] <= 4
+        assert rel(x, ref) <= bound
