@@ -813,7 +813,9 @@ __global__ __launch_bounds__(256) void k_diffuse_nut_adj(Params<T> P, const T* _
 // dJ/du_f = (dJ/dU_c[C] + dJ/dU_c'[C]) / 2 over the adjacent cells inside
 // the grid.  kind 0 (mean speeds): dJ/dU_c = (sum over the regions holding
 // c of coef_r) U_c / |U_c|; kind 2 (desired field): (sum of coef_r)
-// (U_c - U_target,c).  coef_r is precomputed by the host.
+// (U_c - U_target,c).  coef_r is precomputed by the host.  The plane
+// objective has a kernel of its own.
+
 // The plane objective at column (i, j): the cell-centre velocity and the
 // porosity interpolated between layers k0 and k0 + 1 with weight t, and
 // s = sqrt(|u_p|^2 + 1e-12), as the forward evaluates them.
@@ -845,18 +847,8 @@ template <class T>
 __device__ __forceinline__ T seed_cell(const Params<T>& P, const T* __restrict__ U, const T* __restrict__ V,
                                        const T* __restrict__ W, const int* __restrict__ boxes,
                                        const double* __restrict__ coef, int nreg, int kind,
-                                       const T* __restrict__ ut, const PlaneSeed& ps, const T* __restrict__ PHI,
-                                       int C, int i, int j, int k) {
+                                       const T* __restrict__ ut, int C, int i, int j, int k) {
   const Layout& L = P.L;
-  if (kind == 1) {
-    // dJ/ds = area phi_p (2 (s - s_t) - 2 w max(0, s_min - s)), ds/du_p = u_p / s
-    if (k != ps.k0 && k != ps.k0 + 1) return T(0);
-    double up[3], phip, s;
-    plane_column(L, U, V, W, PHI, ps, i, j, up, phip, s);
-    const double lo = fmax(0.0, ps.smin - s);
-    const double dJds = ps.area * phip * (2.0 * (s - ps.st) - 2.0 * ps.wpen * lo);
-    return T((k == ps.k0 ? 1.0 - ps.t : ps.t) * dJds * up[C] / s);
-  }
   double cs = 0.0;
   for (int r = 0; r < nreg; ++r) {
     const int* b = boxes + 6 * r;
@@ -875,61 +867,125 @@ __device__ __forceinline__ T seed_cell(const Params<T>& P, const T* __restrict__
   return T(cs * (uc[C] - (double)ut[(size_t)C * n + cidx]));
 }
 
-template <class T>
-__global__ __launch_bounds__(256) void k_objective_seed(Params<T> P, const T* __restrict__ U, const T* __restrict__ V,
-                                                        const T* __restrict__ W, const int* __restrict__ boxes,
-                                                        const double* __restrict__ coef, int nreg, int kind,
-                                                        const T* __restrict__ ut, PlaneSeed ps,
-                                                        const T* __restrict__ PHI, T* __restrict__ out) {
+constexpr int kSeedFaces = 4;   // faces of a thread, a block apart
+
+// The faces of component C in plane i, from face p0 of the plane on.
+template <int C, class T>
+__device__ __forceinline__ void seed_faces(const Params<T>& P, const T* __restrict__ U, const T* __restrict__ V,
+                                           const T* __restrict__ W, const int* __restrict__ boxes,
+                                           const double* __restrict__ coef, int nreg, int kind,
+                                           const T* __restrict__ ut, T* __restrict__ out, int i, int p0) {
   const Layout& L = P.L;
-  const long long n0 = (long long)(L.nx + 1) * L.ny * L.nz, n1 = (long long)L.nx * (L.ny + 1) * L.nz;
-  const long long n2 = (long long)L.nx * L.ny * (L.nz + 1);
-  const long long ntot = n0 + n1 + n2;
-  for (long long p = (long long)blockIdx.x * blockDim.x + threadIdx.x; p < ntot;
-       p += (long long)gridDim.x * blockDim.x) {
-    int C = 0;
-    long long q = p;
-    if (q >= n0) {
-      q -= n0;
-      C = 1;
-      if (q >= n1) {
-        q -= n1;
-        C = 2;
-      }
-    }
-    const int e0 = L.nx + (C == 0), e1 = L.ny + (C == 1), e2 = L.nz + (C == 2);
-    (void)e0;
-    const int k = (int)(q % e2);
-    const long long r = q / e2;
-    const int j = (int)(r % e1);
-    const int i = (int)(r / e1);
-    const int idx[3] = {i, j, k};
-    const int nC = C == 0 ? L.nx : (C == 1 ? L.ny : L.nz);
+  const int e1 = L.ny + (C == 1), e2 = L.nz + (C == 2), n = e1 * e2;
+  const int nC = C == 0 ? L.nx : (C == 1 ? L.ny : L.nz);
+  T* row = out + (size_t)i * n;
+#pragma unroll
+  for (int u = 0; u < kSeedFaces; ++u) {
+    const int p = p0 + u * 256;
+    if (p >= n) return;
+    const int j = p / e2, k = p - j * e2;
+    const int m = C == 0 ? i : (C == 1 ? j : k);
     T s = T(0);
-    if (idx[C] > 0)
-      s += seed_cell(P, U, V, W, boxes, coef, nreg, kind, ut, ps, PHI, C, i - (C == 0), j - (C == 1), k - (C == 2));
-    if (idx[C] < nC) s += seed_cell(P, U, V, W, boxes, coef, nreg, kind, ut, ps, PHI, C, i, j, k);
-    out[p] = T(0.5) * s;
+    if (m > 0) s += seed_cell(P, U, V, W, boxes, coef, nreg, kind, ut, C, i - (C == 0), j - (C == 1), k - (C == 2));
+    if (m < nC) s += seed_cell(P, U, V, W, boxes, coef, nreg, kind, ut, C, i, j, k);
+    row[p] = T(0.5) * s;
   }
 }
 
-// The plane objective's direct porosity weight: dJ/dphi_p = area ((s - s_t)^2
-// + w max(0, s_min - s)^2), split (1 - t) / t onto layers k0 and k0 + 1.
+// gx blocks per plane of faces normal to x: nx + 1 planes of u, nx of v, nx
+// of w, in the order of the output, faces of a plane by 32-bit index.
 template <class T>
-__global__ __launch_bounds__(256) void k_plane_phi_seed(Layout L, const T* __restrict__ U, const T* __restrict__ V,
-                                                        const T* __restrict__ W, const T* __restrict__ PHI,
-                                                        PlaneSeed ps, double* __restrict__ phibar) {
-  const int n = L.nx * L.ny;
-  for (int c = blockIdx.x * blockDim.x + threadIdx.x; c < n; c += gridDim.x * blockDim.x) {
-    const int i = c / L.ny, j = c % L.ny;
+__global__ __launch_bounds__(256) void k_objective_seed(Params<T> P, int gx, const T* __restrict__ U,
+                                                        const T* __restrict__ V, const T* __restrict__ W,
+                                                        const int* __restrict__ boxes,
+                                                        const double* __restrict__ coef, int nreg, int kind,
+                                                        const T* __restrict__ ut, T* __restrict__ out) {
+  const Layout& L = P.L;
+  const size_t n0 = (size_t)(L.nx + 1) * L.ny * L.nz, n1 = (size_t)L.nx * (L.ny + 1) * L.nz;
+  const int plane = (int)blockIdx.x / gx;
+  const int p0 = ((int)blockIdx.x - plane * gx) * (256 * kSeedFaces) + (int)threadIdx.x;
+  if (plane <= L.nx)
+    seed_faces<0>(P, U, V, W, boxes, coef, nreg, kind, ut, out, plane, p0);
+  else if (plane <= 2 * L.nx)
+    seed_faces<1>(P, U, V, W, boxes, coef, nreg, kind, ut, out + n0, plane - L.nx - 1, p0);
+  else
+    seed_faces<2>(P, U, V, W, boxes, coef, nreg, kind, ut, out + n0 + n1, plane - 2 * L.nx - 1, p0);
+}
+
+// Zeros, 16 bytes at a time from the first aligned element on.
+template <class T>
+__global__ __launch_bounds__(256) void k_seed_zero(T* __restrict__ out, size_t n) {
+  constexpr size_t V = 16 / sizeof(T);
+  const size_t head = min(n, (size_t)((16 - ((uintptr_t)out & 15)) & 15) / sizeof(T));
+  const size_t nv = (n - head) / V, tail = head + nv * V;
+  uint4* q = reinterpret_cast<uint4*>(out + head);
+  const size_t t = (size_t)blockIdx.x * 256 + threadIdx.x, nt = (size_t)gridDim.x * 256;
+  for (size_t v = t; v < nv; v += nt) q[v] = make_uint4(0, 0, 0, 0);
+  if (t < head) out[t] = T(0);
+  if (t < n - tail) out[tail + t] = T(0);
+}
+
+// The plane objective's seed on the two layers of cells beside the plane:
+// dJ/ds = area phi_p (2 (s - s_t) - 2 w max(0, s_min - s)), ds/du_p = u_p /
+// s; and its direct porosity weight dJ/dphi_p = area ((s - s_t)^2 + w max(0,
+// s_min - s)^2), split (1 - t) / t onto the two layers.  A block evaluates
+// 16 x 16 columns, one per thread, into LDS and writes the faces of the
+// 15 x 15 of them whose lower neighbours it has too.  The rest of the seed
+// is zero and is written before (k_seed_zero, 51 MB at 256x256x64 in FP32).
+// One kernel over all faces spent its time on those, in index arithmetic and
+// in roots and quotients that every wavefront evaluated for the two of its
+// faces that need them: 119 us and 8 for the porosity; these two take 10 and
+// 14 us (the chain of a column's loads, root and quotients bounds the
+// second: 324 blocks).
+constexpr int kPlaneTile = 16;
+
+template <class T>
+__global__ __launch_bounds__(256) void k_plane_seed(Layout L, int gx, const T* __restrict__ U, const T* __restrict__ V,
+                                                    const T* __restrict__ W, const T* __restrict__ PHI, PlaneSeed ps,
+                                                    T* __restrict__ out, double* __restrict__ phibar) {
+  __shared__ T col[3][2][kPlaneTile][kPlaneTile + 1];
+  const int a = threadIdx.x / kPlaneTile, b = threadIdx.x % kPlaneTile;
+  const int bi = (int)blockIdx.x / gx, bj = (int)blockIdx.x - bi * gx;
+  const int i = bi * (kPlaneTile - 1) + a - 1, j = bj * (kPlaneTile - 1) + b - 1;
+  const bool in = i >= 0 && i < L.nx && j >= 0 && j < L.ny, own = a > 0 && b > 0;
+  T c[3][2] = {};
+  if (in) {
     double up[3], phip, s;
     plane_column(L, U, V, W, PHI, ps, i, j, up, phip, s);
     const double lo = fmax(0.0, ps.smin - s);
-    const double d = ps.area * ((s - ps.st) * (s - ps.st) + ps.wpen * lo * lo);
-    const size_t base = ((size_t)i * L.ny + j) * L.nz + ps.k0;
-    phibar[base] += (1.0 - ps.t) * d;
-    phibar[base + 1] += ps.t * d;
+    const double dJds = ps.area * phip * (2.0 * (s - ps.st) - 2.0 * ps.wpen * lo);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      c[q][0] = T((1.0 - ps.t) * dJds * up[q] / s);
+      c[q][1] = T(ps.t * dJds * up[q] / s);
+    }
+    if (phibar && own) {
+      const double d = ps.area * ((s - ps.st) * (s - ps.st) + ps.wpen * lo * lo);
+      const size_t base = ((size_t)i * L.ny + j) * L.nz + ps.k0;
+      phibar[base] += (1.0 - ps.t) * d;
+      phibar[base + 1] += ps.t * d;
+    }
   }
+#pragma unroll
+  for (int q = 0; q < 3; ++q)
+#pragma unroll
+    for (int m = 0; m < 2; ++m) col[q][m][a][b] = c[q][m];
+  __syncthreads();
+  if (!own || i > L.nx || j > L.ny) return;
+  const size_t n0 = (size_t)(L.nx + 1) * L.ny * L.nz, n1 = (size_t)L.nx * (L.ny + 1) * L.nz;
+  T* u = out + ((size_t)i * L.ny + j) * L.nz + ps.k0;
+  T* v = out + n0 + ((size_t)i * (L.ny + 1) + j) * L.nz + ps.k0;
+  T* w = out + n0 + n1 + ((size_t)i * L.ny + j) * (L.nz + 1) + ps.k0;
+#pragma unroll
+  for (int m = 0; m < 2; ++m) {
+    // the sum over the face's cells, from zero in their order
+    if (j < L.ny) u[m] = T(0.5) * (T(0) + col[0][m][a - 1][b] + c[0][m]);
+    if (i < L.nx) v[m] = T(0.5) * (T(0) + col[1][m][a][b - 1] + c[1][m]);
+  }
+  if (!in) return;
+  w[0] = T(0.5) * (T(0) + c[2][0]);
+  w[1] = T(0.5) * (T(0) + c[2][0] + c[2][1]);
+  w[2] = T(0.5) * (T(0) + c[2][1]);
 }
 
 // ----------------------------------------------------------------- launchers
@@ -1000,19 +1056,23 @@ template <class T>
 void launch_objective_seed(Grid& g, const Params<T>& P, const int* boxes_dev, const double* coef_dev, int nreg,
                            int kind, const void* ut, void* out, const double plane[6], double* phibar) {
   const Layout& L = P.L;
-  const long long n = (long long)(L.nx + 1) * L.ny * L.nz + (long long)L.nx * (L.ny + 1) * L.nz +
-                      (long long)L.nx * L.ny * (L.nz + 1);
-  const int blocks = (int)std::min<long long>((n + 255) / 256, 16384);
   void* const* Q = g.Q[g.cur];
-  PlaneSeed ps{0, 0.0, 0.0, 0.0, 0.0, 0.0};
-  if (plane) ps = PlaneSeed{(int)plane[0], plane[1], plane[2], plane[3], plane[4], plane[5]};
-  hipLaunchKernelGGL(k_objective_seed<T>, dim3(blocks), dim3(256), 0, g.stream, P, (const T*)Q[0], (const T*)Q[1],
-                     (const T*)Q[2], boxes_dev, coef_dev, nreg, kind, (const T*)ut, ps, (const T*)g.PHI, (T*)out);
-  if (plane && phibar) {
-    const int cols = L.nx * L.ny;
-    hipLaunchKernelGGL(k_plane_phi_seed<T>, dim3(std::min(8192, (cols + 255) / 256)), dim3(256), 0, g.stream, L,
-                       (const T*)Q[0], (const T*)Q[1], (const T*)Q[2], (const T*)g.PHI, ps, phibar);
+  if (!plane) {
+    const int gx = (std::max((L.ny + 1) * L.nz, L.ny * (L.nz + 1)) + 256 * kSeedFaces - 1) / (256 * kSeedFaces);
+    hipLaunchKernelGGL(k_objective_seed<T>, dim3((unsigned)gx * (unsigned)(3 * L.nx + 1)), dim3(256), 0, g.stream, P,
+                       gx, (const T*)Q[0], (const T*)Q[1], (const T*)Q[2], boxes_dev, coef_dev, nreg, kind,
+                       (const T*)ut, (T*)out);
+    return;
   }
+  const size_t n = (size_t)(L.nx + 1) * L.ny * L.nz + (size_t)L.nx * (L.ny + 1) * L.nz +
+                   (size_t)L.nx * L.ny * (L.nz + 1);
+  const PlaneSeed ps{(int)plane[0], plane[1], plane[2], plane[3], plane[4], plane[5]};
+  const size_t zb = (n * sizeof(T) / 16 + 1023) / 1024 + 1;   // four stores per thread
+  hipLaunchKernelGGL(k_seed_zero<T>, dim3((unsigned)zb), dim3(256), 0, g.stream, (T*)out, n);
+  constexpr int own = kPlaneTile - 1;
+  const int gx = L.ny / own + 1;
+  hipLaunchKernelGGL(k_plane_seed<T>, dim3((unsigned)gx * (unsigned)(L.nx / own + 1)), dim3(256), 0, g.stream, L, gx,
+                     (const T*)Q[0], (const T*)Q[1], (const T*)Q[2], (const T*)g.PHI, ps, (T*)out, phibar);
 }
 
 static inline int cell_blocks(const Layout& L) {
