@@ -2,8 +2,8 @@
 // the projection), the porosity -> drag-coefficient map (Sec. 3 drag law),
 // boundary refresh of cell fields and packing between the padded storage
 // and the compact layouts of the C ABI.
+#include "march.h"
 #include "turb_model.h"
-#include "uf_internal.h"
 
 namespace uf {
 
@@ -46,57 +46,135 @@ __device__ __forceinline__ bool cell_block(const Layout& L, int& bx, int& i) {
 // nu_t = k / omega~ limited to [0, nu_max - nu] (the paper's von Neumann
 // viscosity limiter).  Forward Euler with first-order upwind advection and
 // central Laplacians.
-template <class T>
-__device__ __forceinline__ void turb_cells(const Params<T>& P, const T* __restrict__ U, const T* __restrict__ V, const T* __restrict__ W, const T* __restrict__ K0, const T* __restrict__ W0, T* __restrict__ K1, T* __restrict__ W1, T* __restrict__ NUT, int update_kw, int* nf, int bx, int ib) {
-  const Layout& L = P.L;
-  UF_CELL_POINT(L, bx, ib);
-  const long long SX = L.SX, PZ = L.PZ;
-  const long long o = L.at(i, j, k);
+// get(a, dx, dj, dk): array a (u, v, w, k, omega) at the cell displaced by
+// (dx, dj, dk).  Returns the new eddy viscosity; kn and wn when update_kw.
+template <class T, class G>
+__device__ __forceinline__ T turb_cell(const Params<T>& P, G get, bool update_kw, T& kn, T& wn) {
   const T h0 = T(0.5) * P.ih[0], h1 = T(0.5) * P.ih[1], h2 = T(0.5) * P.ih[2];
   // gradients G[c][d] = d u_c / d x_d
-  const T g00 = (U[o + SX] - U[o]) * P.ih[0];
-  const T g11 = (V[o + PZ] - V[o]) * P.ih[1];
-  const T g22 = (W[o + 1] - W[o]) * P.ih[2];
-  auto uc = [&](long long q) { return T(0.5) * (U[q] + U[q + SX]); };
-  auto vc = [&](long long q) { return T(0.5) * (V[q] + V[q + PZ]); };
-  auto wc = [&](long long q) { return T(0.5) * (W[q] + W[q + 1]); };
-  const T g01 = (uc(o + PZ) - uc(o - PZ)) * h1;
-  const T g02 = (uc(o + 1) - uc(o - 1)) * h2;
-  const T g10 = (vc(o + SX) - vc(o - SX)) * h0;
-  const T g12 = (vc(o + 1) - vc(o - 1)) * h2;
-  const T g20 = (wc(o + SX) - wc(o - SX)) * h0;
-  const T g21 = (wc(o + PZ) - wc(o - PZ)) * h1;
+  const T g00 = (get(0, 1, 0, 0) - get(0, 0, 0, 0)) * P.ih[0];
+  const T g11 = (get(1, 0, 1, 0) - get(1, 0, 0, 0)) * P.ih[1];
+  const T g22 = (get(2, 0, 0, 1) - get(2, 0, 0, 0)) * P.ih[2];
+  auto uc = [&](int dx, int dj, int dk) { return T(0.5) * (get(0, dx, dj, dk) + get(0, dx + 1, dj, dk)); };
+  auto vc = [&](int dx, int dj, int dk) { return T(0.5) * (get(1, dx, dj, dk) + get(1, dx, dj + 1, dk)); };
+  auto wc = [&](int dx, int dj, int dk) { return T(0.5) * (get(2, dx, dj, dk) + get(2, dx, dj, dk + 1)); };
+  const T g01 = (uc(0, 1, 0) - uc(0, -1, 0)) * h1;
+  const T g02 = (uc(0, 0, 1) - uc(0, 0, -1)) * h2;
+  const T g10 = (vc(1, 0, 0) - vc(-1, 0, 0)) * h0;
+  const T g12 = (vc(0, 0, 1) - vc(0, 0, -1)) * h2;
+  const T g20 = (wc(1, 0, 0) - wc(-1, 0, 0)) * h0;
+  const T g21 = (wc(0, 1, 0) - wc(0, -1, 0)) * h1;
   const T s01 = T(0.5) * (g01 + g10), s02 = T(0.5) * (g02 + g20), s12 = T(0.5) * (g12 + g21);
   const T S2 = g00 * g00 + g11 * g11 + g22 * g22 + T(2) * (s01 * s01 + s02 * s02 + s12 * s12);
   const T lim = P.lim_coef * sqrt(S2);
-  const T kk = K0[o], ww = W0[o];
+  const T kk = get(3, 0, 0, 0), ww = get(4, 0, 0, 0);
   const T nut = nmin(nmax(kk / nmax(ww, lim), T(0)), P.cap);
-  if (!update_kw) {
-    store_cell(NUT, P, i, j, k, nut, false, T(0));
-    return;
-  }
-  const T u0 = uc(o), u1 = vc(o), u2 = wc(o);
-  auto adv = [&](const T* q) {
-    const T c = q[o];
-    T a = (nmax(u0, T(0)) * (c - q[o - SX]) + nmin(u0, T(0)) * (q[o + SX] - c)) * P.ih[0];
-    a += (nmax(u1, T(0)) * (c - q[o - PZ]) + nmin(u1, T(0)) * (q[o + PZ] - c)) * P.ih[1];
-    a += (nmax(u2, T(0)) * (c - q[o - 1]) + nmin(u2, T(0)) * (q[o + 1] - c)) * P.ih[2];
+  if (!update_kw) return nut;
+  const T u0 = uc(0, 0, 0), u1 = vc(0, 0, 0), u2 = wc(0, 0, 0);
+  auto adv = [&](int q) {
+    const T c = get(q, 0, 0, 0);
+    T a = (nmax(u0, T(0)) * (c - get(q, -1, 0, 0)) + nmin(u0, T(0)) * (get(q, 1, 0, 0) - c)) * P.ih[0];
+    a += (nmax(u1, T(0)) * (c - get(q, 0, -1, 0)) + nmin(u1, T(0)) * (get(q, 0, 1, 0) - c)) * P.ih[1];
+    a += (nmax(u2, T(0)) * (c - get(q, 0, 0, -1)) + nmin(u2, T(0)) * (get(q, 0, 0, 1) - c)) * P.ih[2];
     return a;
   };
-  auto lap = [&](const T* q) {
-    const T c = q[o];
-    return (q[o + SX] - T(2) * c + q[o - SX]) * P.ih2[0] + (q[o + PZ] - T(2) * c + q[o - PZ]) * P.ih2[1] +
-           (q[o + 1] - T(2) * c + q[o - 1]) * P.ih2[2];
+  auto lap = [&](int q) {
+    const T c = get(q, 0, 0, 0);
+    return (get(q, 1, 0, 0) - T(2) * c + get(q, -1, 0, 0)) * P.ih2[0] +
+           (get(q, 0, 1, 0) - T(2) * c + get(q, 0, -1, 0)) * P.ih2[1] +
+           (get(q, 0, 0, 1) - T(2) * c + get(q, 0, 0, -1)) * P.ih2[2];
   };
-  T kn = kk + P.dt * (-adv(K0) + T(2) * nut * S2 - T(kCmu) * kk * ww + (P.nu + T(kSigmaStar) * nut) * lap(K0));
-  T wn = ww + P.dt * (-adv(W0) + T(2 * kAlpha) * S2 - T(kBeta) * ww * ww + (P.nu + T(kSigma) * nut) * lap(W0));
+  kn = kk + P.dt * (-adv(3) + T(2) * nut * S2 - T(kCmu) * kk * ww + (P.nu + T(kSigmaStar) * nut) * lap(3));
+  wn = ww + P.dt * (-adv(4) + T(2 * kAlpha) * S2 - T(kBeta) * ww * ww + (P.nu + T(kSigma) * nut) * lap(4));
   kn = nmax(kn, P.k_min);
   wn = nmax(wn, P.w_min);
-  if (!(isfinite(kn) && isfinite(wn))) *nf = 1;   // every writer stores 1: no atomic needed
-  const T nut_new = nmin(nmax(kn / nmax(wn, lim), T(0)), P.cap);
-  store_cell(K1, P, i, j, k, kn, true, P.k_in);
-  store_cell(W1, P, i, j, k, wn, true, P.w_in);
-  store_cell(NUT, P, i, j, k, nut_new, false, T(0));
+  return nmin(nmax(kn / nmax(wn, lim), T(0)), P.cap);
+}
+
+// The step at cell (i, j, k), from memory.
+template <class T>
+__device__ __forceinline__ void turb_point(const Params<T>& P, const T* __restrict__ U, const T* __restrict__ V, const T* __restrict__ W, const T* __restrict__ K0, const T* __restrict__ W0, T* __restrict__ K1, T* __restrict__ W1, T* __restrict__ NUT, int update_kw, int* nf, int i, int j, int k) {
+  const Layout& L = P.L;
+  const long long o = L.at(i, j, k);
+  const T* q[5] = {U + o, V + o, W + o, K0 + o, W0 + o};
+  T kn, wn;
+  const T nut = turb_cell(P, [&](int a, int dx, int dj, int dk) { return q[a][dx * L.SX + (long long)dj * L.PZ + dk]; },
+                          update_kw != 0, kn, wn);
+  if (update_kw) {
+    if (!(isfinite(kn) && isfinite(wn))) *nf = 1;   // every writer stores 1: no atomic needed
+    store_cell(K1, P, i, j, k, kn, true, P.k_in);
+    store_cell(W1, P, i, j, k, wn, true, P.w_in);
+  }
+  store_cell(NUT, P, i, j, k, nut, false, T(0));
+}
+
+template <class T>
+__device__ __forceinline__ void turb_cells(const Params<T>& P, const T* __restrict__ U, const T* __restrict__ V, const T* __restrict__ W, const T* __restrict__ K0, const T* __restrict__ W0, T* __restrict__ K1, T* __restrict__ W1, T* __restrict__ NUT, int update_kw, int* nf, int bx, int ib) {
+  UF_CELL_POINT(P.L, bx, ib);
+  turb_point(P, U, V, W, K0, W0, K1, W1, NUT, update_kw, nf, i, j, k);
+}
+
+// The update marching along x (march.h): tiles of the cells off the sides
+// along x and y, blocks of their own for the others.
+template <class T>
+struct TurbArgs {
+  const T* in[5];   // u, v, w, k, omega
+  T* out[3];        // k, omega, nu_t
+  int* nf;
+};
+
+__host__ __device__ inline int turb_edges(const Layout& L) { return 2 * L.nz * (L.ny + (L.nx - 2)); }
+
+template <class T>
+__device__ __forceinline__ void turb_edge(const Params<T>& P, const TurbArgs<T>& M, int e) {
+  const Layout& L = P.L;
+  if (e >= turb_edges(L)) return;
+  const int r = e / L.nz, k = e - r * L.nz;
+  int i, j;
+  if (r < 2 * L.ny) {
+    i = r < L.ny ? 0 : L.nx - 1;
+    j = r < L.ny ? r : r - L.ny;
+  } else {
+    const int q = r - 2 * L.ny;
+    j = q < L.nx - 2 ? 0 : L.ny - 1;
+    i = 1 + (q < L.nx - 2 ? q : q - (L.nx - 2));
+  }
+  turb_point(P, M.in[0], M.in[1], M.in[2], M.in[3], M.in[4], M.out[0], M.out[1], M.out[2], 1, M.nf, i, j, k);
+}
+
+template <int SHAPE, class T>
+__device__ __forceinline__ void turb_march(const Params<T>& P, const March& G, const TurbArgs<T>& M, T* lds, int tile,
+                                           int chunk) {
+  const Layout& L = P.L;
+  Planes<SHAPE, 5, T> A;
+#pragma unroll
+  for (int a = 0; a < 5; ++a) A.src[a] = M.in[a];
+  int j0, k0;
+  const MarchLane c = march_lane<SHAPE>(L, G, tile, L.ny - 2, L.nz + 2, L.nz, L.nz, j0, k0);
+  A.init(L, lds, j0, k0, G.TK);
+  A.q = c.qa;
+  const int i0 = 1 + chunk * G.len;
+  march(A, i0, min(L.nx - 1, i0 + G.len), [&](int i) {
+    if (!c.active) return;
+    T kn, wn;
+    const T nut = turb_cell(P, [&](int a, int dx, int dj, int dk) { return A.at(a, dx, dj, dk); }, true, kn, wn);
+    if (!(isfinite(kn) && isfinite(wn))) *M.nf = 1;
+    const long long o = (long long)(i + 1) * L.SX;   // the ghosts along z copy their cell
+    (M.out[0] + o)[c.oc] = kn;
+    (M.out[1] + o)[c.oc] = wn;
+    (M.out[2] + o)[c.oc] = nut;
+  });
+}
+
+template <int SHAPE, class T>
+__global__ __launch_bounds__(kMarch, sizeof(T) == 4 ? 6 : 2) void k_turb_march(Params<T> P, March G, TurbArgs<T> M,
+                                                                              const int* __restrict__ gate) {
+  __shared__ T lds[Planes<SHAPE, 5, T>::LDS];
+  if (gate && !*gate) return;
+  int tile, chunk;
+  if (!march_block(G, tile, chunk)) return;
+  if (tile < 0) turb_edge(P, M, chunk * kMarch + (int)threadIdx.x);
+  else turb_march<SHAPE>(P, G, M, lds, tile, chunk);
 }
 
 // gate: as k_project's (the step's k-omega update enqueued with it).
@@ -293,6 +371,17 @@ template <class T>
 void launch_turb(Grid& g, const Params<T>& P, void* const Q[3], const void* K0, const void* W0, void* K1, void* W1,
                  void* NUT, int update_kw, const int* gate) {
   TimedLaunch tl(g, UF_TK_TURB);
+  if (update_kw && march_pays(P, kMarchTurb)) {
+    const Layout& L = P.L;
+    const TurbArgs<T> M{{(const T*)Q[0], (const T*)Q[1], (const T*)Q[2], (const T*)K0, (const T*)W0},
+                        {(T*)K1, (T*)W1, (T*)NUT}, nf_word(g)};
+    const March G = march_geom(L.nx - 2, L.ny - 2, L.nz + 2, turb_edges(L));
+    auto go = [&](auto kernel) { launch_k(g, kernel, march_grid(G), dim3(kMarch), P, G, M, gate); };
+    if (G.shape == 0) go(k_turb_march<0, T>);
+    else if (G.shape == 1) go(k_turb_march<1, T>);
+    else go(k_turb_march<2, T>);
+    return;
+  }
   launch_k(g, k_turbulence<T>, cell_grid(P.L), dim3(kCellBlock), P, (const T*)Q[0],
                      (const T*)Q[1], (const T*)Q[2], (const T*)K0, (const T*)W0, (T*)K1, (T*)W1, (T*)NUT, update_kw,
                      nf_word(g), gate);

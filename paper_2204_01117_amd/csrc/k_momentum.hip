@@ -7,7 +7,9 @@
 // (j, k) in [0, ny] x [0, nz], flattened z fastest so that a wavefront
 // reads consecutive memory.  Fixed boundary normal faces get their
 // Dirichlet value; ghosts are written by store_face.
-#include "face_ops.h"
+#include <type_traits>
+
+#include "march.h"
 
 namespace uf {
 
@@ -167,6 +169,117 @@ __global__ __launch_bounds__(kFaceBlock) void k_advect_corr32(Params<T> P, const
   advect_corr32_component(P, U, V, W, Uh, Vh, Wh, Uo, Vo, Wo, e % 3, bx, ib);
 }
 
+// ------------------------------------------------- advection, marching -----
+// Arrays: 0 to 2 the velocity, 3 to 5 (corrector) the predictor's field.
+
+// face_velocity() of the thread's column.
+template <int C, int SHAPE, int NA, class T>
+__device__ __forceinline__ void march_velocity(const Planes<SHAPE, NA, T>& A, T vel[3]) {
+  constexpr int ec[3] = {C == 0, C == 1, C == 2};
+#pragma unroll
+  for (int cp = 0; cp < 3; ++cp) {
+    if (cp == C) {
+      vel[cp] = A.at(cp, 0, 0, 0);
+    } else {
+      const int e[3] = {cp == 0, cp == 1, cp == 2};
+      vel[cp] = T(0.25) * (A.at(cp, -ec[0], -ec[1], -ec[2]) + A.at(cp, e[0] - ec[0], e[1] - ec[1], e[2] - ec[2]) +
+                           A.at(cp, 0, 0, 0) + A.at(cp, e[0], e[1], e[2]));
+    }
+  }
+}
+
+// Are all three displacements of every lane shorter than a cell?  The trace
+// position of a face is then within the padded array (the clamps of
+// trace_axis() do nothing: -1 < n + s < ext for 0 <= n <= ext - 1), its cell
+// is the face's or the one before it, and floor() is a comparison.  Stable
+// time steps keep it so; other wavefronts take the general path.  False for
+// a NaN.
+template <class T>
+__device__ __forceinline__ bool march_near(const T d[3]) {
+  return __all(fabs(d[0]) < T(1) && fabs(d[1]) < T(1) && fabs(d[2]) < T(1));
+}
+
+// The samples and weights of array a at the position displaced by s, near.
+template <int SHAPE, int NA, class T>
+__device__ __forceinline__ void march_samples(const Planes<SHAPE, NA, T>& A, int a, T si, T sj, T sk, Tri<T>& t, T v[8]) {
+  constexpr int PITCH = Planes<SHAPE, NA, T>::PITCH, PL = Planes<SHAPE, NA, T>::PL;
+  const bool bi = si < T(0), bj = sj < T(0), bk = sk < T(0);
+  t.ti = si + (bi ? T(1) : T(0));
+  t.tj = sj + (bj ? T(1) : T(0));
+  t.tk = sk + (bk ? T(1) : T(0));
+  const int q = A.q + (bj ? -PITCH : 0) + (bk ? -1 : 0);
+  const T* lo = A.lds + (q + (bi ? A.s[0] : A.s[1])) + a * PL;
+  const T* hi = A.lds + (q + (bi ? A.s[1] : A.s[2])) + a * PL;
+  v[0] = lo[0];
+  v[1] = hi[0];
+  v[2] = lo[PITCH];
+  v[3] = hi[PITCH];
+  v[4] = lo[1];
+  v[5] = hi[1];
+  v[6] = lo[PITCH + 1];
+  v[7] = hi[PITCH + 1];
+}
+
+template <int C, int SHAPE, class T>
+__device__ __forceinline__ T march_fwd(const Params<T>& P, const Planes<SHAPE, 3, T>& A, int i, int j, int k) {
+  T vel[3];
+  march_velocity<C>(A, vel);
+  const T d[3] = {vel[0] * P.dth[0], vel[1] * P.dth[1], vel[2] * P.dth[2]};
+  if (march_near(d)) {
+    Tri<T> t;
+    T v[8];
+    march_samples(A, C, -d[0], -d[1], -d[2], t, v);
+    return tri_eval(t, v);
+  }
+  T mn, mx;
+  return sample<C, false>(P.L, A.src[C], i, j, k, -d[0], -d[1], -d[2], &mn, &mx) + nan_if<T>(any_nan3(vel));
+}
+
+template <int C, int SHAPE, class T>
+__device__ __forceinline__ T march_corr(const Params<T>& P, const Planes<SHAPE, 6, T>& A, int i, int j, int k) {
+  T vel[3];
+  march_velocity<C>(A, vel);
+  const T d[3] = {vel[0] * P.dth[0], vel[1] * P.dth[1], vel[2] * P.dth[2]};
+  T qh, qc, mn, mx, nan = T(0);
+  if (march_near(d)) {
+    Tri<T> t;
+    T v[8];
+    march_samples(A, C, -d[0], -d[1], -d[2], t, v);
+    tri_range(v, mn, mx);
+    qh = tri_eval(t, v);
+    march_samples(A, 3 + C, d[0], d[1], d[2], t, v);
+    qc = tri_eval(t, v);
+  } else {
+    T d0, d1;
+    qh = sample<C, true>(P.L, A.src[C], i, j, k, -d[0], -d[1], -d[2], &mn, &mx);
+    qc = sample<C, false>(P.L, A.src[3 + C], i, j, k, d[0], d[1], d[2], &d0, &d1);
+    nan = nan_if<T>(any_nan3(vel));
+  }
+  const T qt = qh + T(0.5) * (vel[C] - qc);
+  return nmin(nmax(qt, mn), mx) + nan;
+}
+
+// One explicit diffusion step; array 3 is the eddy viscosity.
+template <int C, int SHAPE, class T>
+__device__ __forceinline__ T march_diffuse(const Params<T>& P, const Planes<SHAPE, 4, T>& A) {
+  const T qc = A.at(C, 0, 0, 0);
+  const T lap = (A.at(C, 1, 0, 0) - T(2) * qc + A.at(C, -1, 0, 0)) * P.ih2[0] +
+                (A.at(C, 0, 1, 0) - T(2) * qc + A.at(C, 0, -1, 0)) * P.ih2[1] +
+                (A.at(C, 0, 0, 1) - T(2) * qc + A.at(C, 0, 0, -1)) * P.ih2[2];
+  const T nuf = P.nu + T(0.5) * (A.at(3, -(C == 0), -(C == 1), -(C == 2)) + A.at(3, 0, 0, 0));
+  return qc + P.dt * nuf * lap;
+}
+
+// The porosity drag; array 3 is the drag coefficient.
+template <int C, int SHAPE, class T>
+__device__ __forceinline__ T march_drag(const Params<T>& P, const Planes<SHAPE, 4, T>& A) {
+  T vel[3];
+  march_velocity<C>(A, vel);
+  const T speed = sqrt(vel[0] * vel[0] + vel[1] * vel[1] + vel[2] * vel[2]);
+  const T cf = T(0.5) * (A.at(3, -(C == 0), -(C == 1), -(C == 2)) + A.at(3, 0, 0, 0));
+  return nmax(T(0), T(1) - P.dt * cf * speed) * vel[C];
+}
+
 // ------------------------------------------------------------- diffusion --
 template <int C, class T>
 __device__ __forceinline__ T diffuse_value(const Params<T>& P, const T* __restrict__ q, const T* __restrict__ nut,
@@ -233,6 +346,98 @@ __global__ __launch_bounds__(kFaceBlock) void k_drag(Params<T> P, const T* __res
   int bx, ib;
   if (!face_block(P.L, bx, ib)) return;
   drag_faces(P, U, V, W, Cc, Uo, Vo, Wo, nf, bx, ib);
+}
+
+// ------------------------------------------ the stages that march along x --
+// What a stage reads (the velocity first) and writes.
+template <class T>
+struct MarchArgs {
+  const T* in[6];
+  T* out[3];
+  int* nf;
+};
+
+constexpr int march_arrays(int stage) { return stage == MS_ADVECT_CORR ? 6 : stage == MS_ADVECT_FWD ? 3 : 4; }
+
+template <int STAGE, int C, int SHAPE, int NA, class T>
+__device__ __forceinline__ T march_value(const Params<T>& P, const Planes<SHAPE, NA, T>& A, int i, int j, int k) {
+  if constexpr (STAGE == MS_ADVECT_FWD) return march_fwd<C>(P, A, i, j, k);
+  else if constexpr (STAGE == MS_ADVECT_CORR) return march_corr<C>(P, A, i, j, k);
+  else if constexpr (STAGE == MS_DIFFUSE) return march_diffuse<C>(P, A);
+  else return march_drag<C>(P, A);
+}
+
+template <int STAGE, int SHAPE, class T>
+__device__ __forceinline__ void march_faces(const Params<T>& P, const March& G, const MarchArgs<T>& M, T* lds, int tile,
+                                            int chunk) {
+  const Layout& L = P.L;
+  Planes<SHAPE, march_arrays(STAGE), T> A;
+#pragma unroll
+  for (int a = 0; a < march_arrays(STAGE); ++a) A.src[a] = M.in[a];
+  int j0, k0;
+  MarchLane c = march_lane<SHAPE>(L, G, tile, L.ny - 2, L.nz + 3, L.nz, L.nz + 1, j0, k0);
+  A.init(L, lds, j0, k0, G.TK);
+  const int i0 = 1 + chunk * G.len;
+  march(A, i0, min(L.nx - 1, i0 + G.len), [&](int i) {
+    if (!c.active) return;
+    auto face = [&](auto tag) {
+      constexpr int C = decltype(tag)::value;
+      A.q = C == 2 ? c.qb : c.qa;
+      const T v = march_value<STAGE, C>(P, A, i, c.j, min(max(c.k, 0), C == 2 ? L.nz : L.nz - 1));
+      // a NaN/Inf raises the state's non-finite flag (every writer stores 1,
+      // so the race is benign)
+      if (STAGE == MS_DRAG && !isfinite(v)) *M.nf = 1;
+      march_put<C>(P, M.out[C], c, i, v);
+    };
+    face(std::integral_constant<int, 0>());
+    face(std::integral_constant<int, 1>());
+    face(std::integral_constant<int, 2>());
+  });
+}
+
+// The corners beside the sides along x (i = 0, nx - 1, nx) and y (j = 0, ny -
+// 1, ny), which the tiles leave out: corner e of them, from memory.
+__host__ __device__ inline int march_edges(const Layout& L) { return 3 * (L.nz + 1) * ((L.ny + 1) + (L.nx - 2)); }
+
+template <int STAGE, class T>
+__device__ __forceinline__ void march_edge(const Params<T>& P, const MarchArgs<T>& M, int e) {
+  const Layout& L = P.L;
+  if (e >= march_edges(L)) return;
+  const int r = e / (L.nz + 1), k = e - r * (L.nz + 1);
+  int i, j;
+  if (r < 3 * (L.ny + 1)) {
+    const int s = r / (L.ny + 1);
+    i = s == 0 ? 0 : L.nx - 2 + s;
+    j = r - s * (L.ny + 1);
+  } else {
+    const int q = r - 3 * (L.ny + 1), s = q / (L.nx - 2);
+    j = s == 0 ? 0 : L.ny - 2 + s;
+    i = 1 + q - s * (L.nx - 2);
+  }
+  const long long o = L.at(i, j, k);
+  const T *U = M.in[0], *V = M.in[1], *W = M.in[2];
+  auto face = [&](auto tag) {
+    constexpr int C = decltype(tag)::value;
+    T v;
+    if constexpr (STAGE == MS_ADVECT_FWD) v = advect_fwd_value<C>(P, U, V, W, o, i, j, k);
+    else if constexpr (STAGE == MS_ADVECT_CORR) v = advect_corr_value<C>(P, U, V, W, M.in[3 + C], o, i, j, k);
+    else if constexpr (STAGE == MS_DIFFUSE) v = diffuse_value<C>(P, M.in[C], M.in[3], o);
+    else v = drag_value<C>(P, U, V, W, M.in[3], o);
+    if (STAGE == MS_DRAG && !isfinite(v) && owns_face<C, T>(L, i, j, k)) *M.nf = 1;
+    finish_face<C>(P, M.out[C], i, j, k, v);
+  };
+  face(std::integral_constant<int, 0>());
+  face(std::integral_constant<int, 1>());
+  face(std::integral_constant<int, 2>());
+}
+
+template <int STAGE, int SHAPE, class T>
+__global__ __launch_bounds__(kMarch, sizeof(T) == 4 ? 6 : 2) void k_march(Params<T> P, March G, MarchArgs<T> M) {
+  __shared__ T lds[Planes<SHAPE, march_arrays(STAGE), T>::LDS];
+  int tile, chunk;
+  if (!march_block(G, tile, chunk)) return;
+  if (tile < 0) march_edge<STAGE>(P, M, chunk * kMarch + (int)threadIdx.x);
+  else march_faces<STAGE, SHAPE>(P, G, M, lds, tile, chunk);
 }
 
 // ------------------------------------------------ projection (velocity part)
@@ -345,9 +550,33 @@ void launch_faces_multi(int stage, const MultiCase<T>* mc, const CaseStarts& cs,
 // ----------------------------------------------------------------- launchers
 static inline dim3 face_grid(const Layout& L) { return xcd_grid(face_gx(L), L.nx + 1); }
 
+template <int STAGE, class T>
+static void launch_march(Grid& g, const Params<T>& P, void* const Q[3], void* const H[3], const void* cells,
+                         void* const O[3]) {
+  const Layout& L = P.L;
+  MarchArgs<T> M{{(const T*)Q[0], (const T*)Q[1], (const T*)Q[2]}, {(T*)O[0], (T*)O[1], (T*)O[2]}, nf_word(g)};
+  M.in[3] = (const T*)(H ? H[0] : cells);
+  if (H)
+    for (int c = 1; c < 3; ++c) M.in[3 + c] = (const T*)H[c];
+  const March G = march_geom(L.nx - 2, L.ny - 2, L.nz + 3, march_edges(L));
+  auto go = [&](auto kernel) { launch_k(g, kernel, march_grid(G), dim3(kMarch), P, G, M); };
+  if (G.shape == 0) go(k_march<STAGE, 0, T>);
+  else if (G.shape == 1) go(k_march<STAGE, 1, T>);
+  else go(k_march<STAGE, 2, T>);
+}
+
 template <class T>
 void launch_advect(Grid& g, const Params<T>& P, void* const Qin[3], void* const Qhat[3], void* const Qout[3]) {
   const dim3 grid = face_grid(P.L);
+  if (march_pays(P, kMarchFaces)) {
+    {
+      TimedLaunch tl(g, UF_TK_ADVECT_FWD);
+      launch_march<MS_ADVECT_FWD, T>(g, P, Qin, nullptr, nullptr, Qhat);
+    }
+    TimedLaunch tl(g, UF_TK_ADVECT_CORR);
+    launch_march<MS_ADVECT_CORR, T>(g, P, Qin, Qhat, nullptr, Qout);
+    return;
+  }
   if (offsets_fit_32(P.L, sizeof(T))) {
     {
       TimedLaunch tl(g, UF_TK_ADVECT_FWD);
@@ -374,6 +603,7 @@ void launch_advect(Grid& g, const Params<T>& P, void* const Qin[3], void* const 
 template <class T>
 void launch_diffuse(Grid& g, const Params<T>& P, void* const Qin[3], void* const Qout[3]) {
   TimedLaunch tl(g, UF_TK_DIFFUSE);
+  if (march_pays(P, kMarchFaces)) return launch_march<MS_DIFFUSE, T>(g, P, Qin, nullptr, g.NUT, Qout);
   launch_k(g, k_diffuse<T>, face_grid(P.L), dim3(kFaceBlock), P, (const T*)Qin[0],
                      (const T*)Qin[1], (const T*)Qin[2], (const T*)g.NUT, (T*)Qout[0], (T*)Qout[1], (T*)Qout[2]);
 }
@@ -381,6 +611,7 @@ void launch_diffuse(Grid& g, const Params<T>& P, void* const Qin[3], void* const
 template <class T>
 void launch_drag(Grid& g, const Params<T>& P, void* const Qin[3], void* const Qout[3]) {
   TimedLaunch tl(g, UF_TK_DRAG);
+  if (march_pays(P, kMarchFaces)) return launch_march<MS_DRAG, T>(g, P, Qin, nullptr, g.C, Qout);
   launch_k(g, k_drag<T>, face_grid(P.L), dim3(kFaceBlock), P, (const T*)Qin[0], (const T*)Qin[1],
                      (const T*)Qin[2], (const T*)g.C, (T*)Qout[0], (T*)Qout[1], (T*)Qout[2], nf_word(g));
 }

@@ -1,0 +1,77 @@
+"""The stages that march along x over tiles of a plane against FP64, at
+the sizes where the tiling can go wrong: z extents that fill, overflow and
+split a tile's rows in each of its three shapes, y extents at the edges of
+the tile rows, chunks of planes with a remainder, sides of every kind along
+x and y; and a velocity so large that traces leave the neighbouring cells.
+
+Each grid has at least 2.5 million cells, from which the k-omega update
+marches too, and the FP64 library's kernels take a thread per corner; so the
+same state is advanced by both.
+
+Tolerance: the suite's for one FP32 step from an identical state, 1e-5 in
+relative L2 per field (one wrong cell in a few million of a tenth of the
+largest value would exceed it)."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+pytestmark = pytest.mark.gpu
+
+from uf_layouts import default_config  # noqa: E402
+from uf_layouts.configs import BC_INLET, BC_OUTLET, BC_SLIP, BC_WALL, PC_MG, STAGE_ADVECT  # noqa: E402
+
+O, I, W, S = BC_OUTLET, BC_INLET, BC_WALL, BC_SLIP
+CASES = [
+    ((150, 240, 70), [I, O, S, S, W, S]),    # 73 lanes: a full row, one tile along z
+    ((150, 240, 71), [I, O, I, O, W, S]),    # 74: two tiles
+    ((200, 290, 43), [O, I, S, S, W, O]),    # 46: the second shape's full row
+    ((127, 1000, 20), [I, O, W, S, W, S]),   # 23: the third's
+    ((61, 301, 144), [I, O, S, S, W, W]),    # 147: three tiles
+]
+
+
+def advanced(n, bc, scale, fields, **over):
+    """The fields after one step from the same state, in FP64 and FP32."""
+    import paper_2204_01117_amd as U
+    rng = np.random.default_rng(n[2])
+    out, start = [], None
+    for dtype in ("f64", "f32"):
+        cfg = default_config(*n, 2.0, dy=2.1, dz=1.9, dt=0.05, dtype=dtype, bc=bc, u_ref=4.0, precond=PC_MG,
+                             cg_tol=1e-10 if dtype == "f64" else 1e-6, cg_maxit=50, **over)
+        g = U.Grid(cfg)
+        if start is None:
+            phi = np.ones(n)
+            phi[n[0] // 3:n[0] // 2, n[1] // 3:n[1] // 2, :n[2] // 2] = 0.1
+            st = g.state()
+            # smooth waves, so that FP32 and FP64 clamp the same samples
+            start = {}
+            for f in st:
+                t = st[f].double().cpu().numpy()
+                x = [np.arange(m) / m for m in t.shape]
+                wave = (np.sin(2 * np.pi * (2 * x[0][:, None, None] + rng.uniform())) *
+                        np.sin(2 * np.pi * (3 * x[1][None, :, None] + rng.uniform())) *
+                        np.cos(np.pi * x[2][None, None, :]))
+                t = t + 0.3 * wave if f in "uvw" else t * (1 + 0.1 * wave)
+                start[f] = torch.as_tensor((scale * t if f in "uvw" else t).astype(np.float32))
+        g.set_porosity(torch.as_tensor(phi))
+        g.set_state({f: t.to(torch.float64 if dtype == "f64" else torch.float32) for f, t in start.items()})
+        g.step(1)
+        out.append({f: t.double().cpu() for f, t in g.state().items()})
+        g.close()
+    for f in fields:
+        ref = torch.cat([out[0][c].ravel() for c in "uvw"]) if f in "uvw" else out[0][f]
+        err = float((out[1][f] - out[0][f]).norm() / ref.norm())
+        print(n, scale, f, err, flush=True)
+        assert err <= 1e-5
+
+
+@pytest.mark.parametrize("n,bc", CASES)
+def test_march_step_against_fp64(n, bc):
+    advanced(n, bc, 1.0, ("u", "v", "w", "k", "omega"))
+
+
+def test_march_advection_past_a_cell():
+    """Displacements up to about two cells (advection alone: at such time
+    steps the other stages amplify the FP32 rounding of the state)."""
+    advanced((150, 240, 70), [I, O, S, S, W, S], 10.0, ("u", "v", "w"), stages=STAGE_ADVECT)
