@@ -138,11 +138,15 @@ struct CellDiv {
     x0 = P.bc[0] == INLET ? -lu : T(0);
     x1 = P.bc[1] == INLET ? lu : T(0);
   }
+  // the six faces of cell i: lower and upper along x, y, z
+  __device__ __forceinline__ T of(const Params<T>& P, T u0, T u1, T v0, T v1, T w0, T w1, int i) const {
+    const T rest = yz + (i == 0 ? x0 : T(0)) + (i == P.L.nx - 1 ? x1 : T(0));
+    return (u1 - u0) * P.ih[0] + (v1 - v0) * P.ih[1] + (w1 - w0) * P.ih[2] + rest;
+  }
   __device__ __forceinline__ T at(const Params<T>& P, const T* __restrict__ U, const T* __restrict__ V,
                                   const T* __restrict__ W, long long o, int i) const {
     const Layout& L = P.L;
-    const T rest = yz + (i == 0 ? x0 : T(0)) + (i == L.nx - 1 ? x1 : T(0));
-    return (U[o + L.SX] - U[o]) * P.ih[0] + (V[o + L.PZ] - V[o]) * P.ih[1] + (W[o + 1] - W[o]) * P.ih[2] + rest;
+    return of(P, U[o], U[o + L.SX], V[o], V[o + L.PZ], W[o], W[o + 1], i);
   }
 };
 
@@ -152,7 +156,11 @@ struct CellDiv {
 // far smaller than x and round accordingly: with D x minus the neighbours'
 // sum, the rounding relative to x itself, turned into an error of the
 // smooth modes by A^-1, was the largest part of the FP32 pressure's error
-// (512x512x128: 1.5e-6 to 7e-6 of the pressure).
+// (512x512x128: 1.5e-6 to 7e-6 of the pressure).  Bound by the latency of its
+// loads: a thread takes kInitCells cells along x at a time, whose loads are
+// all in flight together (251 -> 146 us at 512x512x128, 28 -> 20 at 256x256x64).
+constexpr int kInitCells = 4;
+
 template <class T>
 __global__ __launch_bounds__(kCgBlock) void k_cg_init(Params<T> P, const T* __restrict__ U, const T* __restrict__ V,
                                                       const T* __restrict__ W, const T* __restrict__ bin,
@@ -164,19 +172,43 @@ __global__ __launch_bounds__(kCgBlock) void k_cg_init(Params<T> P, const T* __re
     const long long ym = j == 0 && P.bc[2] != OUTLET ? 0 : -L.PZ, yp = j == L.ny - 1 && P.bc[3] != OUTLET ? 0 : L.PZ;
     const long long zm = k == 0 && P.bc[4] != OUTLET ? 0 : -1, zp = k == L.nz - 1 && P.bc[5] != OUTLET ? 0 : 1;
     const CellDiv<T> div(P, j, k);
-    long long o = L.at(i0, j, k);
-    T xm = X[o - L.SX], xc = X[o];
-    for (int i = i0; i < i1; ++i, o += L.SX) {
-      const T xp = X[o + L.SX];
-      const T b = bin ? bin[o] : -P.rho_dt * div.at(P, U, V, W, o, i);
-      const T wm = i == 0 && P.bc[0] != OUTLET ? T(0) : P.ih2[0], wp = i == L.nx - 1 && P.bc[1] != OUTLET ? T(0) : P.ih2[0];
-      const T r = b + (wm * (xm - xc) + wp * (xp - xc) + P.ih2[1] * ((X[o + yp] - xc) + (X[o + ym] - xc)) +
-                       P.ih2[2] * ((X[o + zp] - xc) + (X[o + zm] - xc)));
-      R[o] = r;
-      v[0] += (double)b * (double)b;
-      v[1] += (double)r * (double)r;
-      xm = xc;
-      xc = xp;
+    const long long o0 = L.at(i0, j, k);
+    T xm = X[o0 - L.SX], xc = X[o0], u0 = bin ? T(0) : U[o0];
+    for (int i = i0; i < i1; i += kInitCells) {
+      T xp[kInitCells], n[kInitCells][4], f[kInitCells][5];   // neighbours of x; faces, or b
+#pragma unroll
+      for (int q = 0; q < kInitCells; ++q) {
+        const long long o = o0 + (long long)(min(i + q, i1 - 1) - i0) * L.SX;
+        xp[q] = X[o + L.SX];
+        n[q][0] = X[o + yp];
+        n[q][1] = X[o + ym];
+        n[q][2] = X[o + zp];
+        n[q][3] = X[o + zm];
+        if (bin) {
+          f[q][0] = bin[o];
+        } else {
+          f[q][0] = U[o + L.SX];
+          f[q][1] = V[o];
+          f[q][2] = V[o + L.PZ];
+          f[q][3] = W[o];
+          f[q][4] = W[o + 1];
+        }
+      }
+#pragma unroll
+      for (int q = 0; q < kInitCells; ++q) {
+        if (i + q >= i1) break;
+        const T b = bin ? f[q][0] : -P.rho_dt * div.of(P, u0, f[q][0], f[q][1], f[q][2], f[q][3], f[q][4], i + q);
+        const T wm = i + q == 0 && P.bc[0] != OUTLET ? T(0) : P.ih2[0];
+        const T wp = i + q == L.nx - 1 && P.bc[1] != OUTLET ? T(0) : P.ih2[0];
+        const T r = b + (wm * (xm - xc) + wp * (xp[q] - xc) + P.ih2[1] * ((n[q][0] - xc) + (n[q][1] - xc)) +
+                         P.ih2[2] * ((n[q][2] - xc) + (n[q][3] - xc)));
+        R[o0 + (long long)(i + q - i0) * L.SX] = r;
+        v[0] += (double)b * (double)b;
+        v[1] += (double)r * (double)r;
+        xm = xc;
+        xc = xp[q];
+        u0 = f[q][0];
+      }
     }
   }
   const int slots[2] = {S_BB, S_RR};

@@ -12,7 +12,7 @@
 // (neighbours are immediate offsets), and the rules of the boundary stay out
 // of the loop: the planes and rows beside the sides along x and y are left to
 // blocks of their own, a thread per corner (with the rules in the loop the
-// predictor took 55 us at 256x256x64, the diffusion 49; without 37 and 30),
+// predictor took 55 us at 256x256x64, without 37),
 // and the ghosts beyond the sides along z, of which nearly every
 // wavefront has some, have lanes that evaluate the nearest face and store it
 // by the side's rule (MarchLane): one store per component without a branch.
@@ -21,8 +21,6 @@
 //                256x256x64   450x300x40   512x512x128
 //   predictor     69 ->  37    98 ->  48   479 -> 273
 //   corrector    113 ->  62   139 ->  78   751 -> 457
-//   diffusion     43 ->  30    64 ->  46   347 -> 290
-//   drag          51 ->  39    70 ->  49   353 -> 290
 //   k-omega       54 ->  46    75 ->  62   451 -> 352
 // (the gathering kernels depend on the flow too: 124, 166 and 860 us for the
 // corrector of a less regular state; these do not).
@@ -93,9 +91,9 @@ inline March march_geom(int ni, int nj, int nk, int nedge) {
 
 // Where marching is the faster way: with too few blocks a CU cannot hide the
 // time a block takes per plane.  In FP32 from a quarter of a million corners
-// for the momentum stages (predictor, corrector, diffusion and drag together,
-// us, against a thread per corner: 96x64x32 37.7 against 37.9, 129x97x35 43.7
-// against 48.6, 256x256x64 171 against 291) and from 2.5 million cells for
+// for the advection (predictor and corrector together, us, against a thread
+// per corner: 96x64x32 20.5 against 22.4, 129x97x35 24.3 against 30.3,
+// 256x256x64 101 against 197) and from 2.5 million cells for
 // the k-omega update, whose gathers are fewer (200x200x40 21.5 against 18.8,
 // 256x256x64 46.5 against 53.7).  In FP64 the planes in LDS leave one block
 // per CU.
@@ -224,19 +222,19 @@ __device__ __forceinline__ MarchLane march_lane(const Layout& L, const March& G,
   return c;
 }
 
-// Stores the value v of component C, evaluated at the face nearest to the
-// lane, off the sides along x and y and with no inlet along z.  out: the
-// padded array.
+// Stores the value v of component C, evaluated at the face nearest to the lane
+// at k, off the sides along x and y and with no inlet along z.  out: the
+// padded array; oc: the lane's column in a plane of it.
 template <int C, class T>
-__device__ __forceinline__ void march_put(const Params<T>& P, T* __restrict__ out, const MarchLane& c, int i, T v) {
+__device__ __forceinline__ void march_put(const Params<T>& P, T* __restrict__ out, int k, unsigned oc, int i, T v) {
   const Layout& L = P.L;
   T* p = out + (long long)(i + 1) * L.SX;
   if (C == 2) {
-    if ((c.k <= 0 && P.bc[4] != OUTLET) || (c.k >= L.nz && P.bc[5] != OUTLET)) v = T(0);   // fixed faces
-    p[c.oc] = v;
+    if ((k <= 0 && P.bc[4] != OUTLET) || (k >= L.nz && P.bc[5] != OUTLET)) v = T(0);   // fixed faces
+    p[oc] = v;
   } else {
-    if ((c.k < 0 && P.bc[4] == WALL) || (c.k >= L.nz && P.bc[5] == WALL)) v = -v;
-    if (c.k <= L.nz) p[c.oc] = v;
+    if ((k < 0 && P.bc[4] == WALL) || (k >= L.nz && P.bc[5] == WALL)) v = -v;
+    if (k <= L.nz) p[oc] = v;
   }
 }
 

@@ -1,12 +1,14 @@
-"""The stages that march along x over tiles of a plane against FP64, at
+"""The large grids' stages -- marching along x over tiles of a plane, or
+several planes per thread -- against FP64, at
 the sizes where the tiling can go wrong: z extents that fill, overflow and
 split a tile's rows in each of its three shapes, y extents at the edges of
 the tile rows, chunks of planes with a remainder, sides of every kind along
 x and y; and a velocity so large that traces leave the neighbouring cells.
 
 Each grid has at least 2.5 million cells, from which the k-omega update
-marches too, and the FP64 library's kernels take a thread per corner; so the
-same state is advanced by both.
+marches too.  The FP64 library's advection and k-omega kernels take a thread
+per corner, and an outlet above takes diffusion and drag back to those; the
+same state is advanced by both types.
 
 Tolerance: the suite's for one FP32 step from an identical state, 1e-5 in
 relative L2 per field (one wrong cell in a few million of a tenth of the
