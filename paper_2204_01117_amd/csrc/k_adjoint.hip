@@ -21,7 +21,9 @@
 // An adjoint array holds the derivative of the objective with respect to
 // the interior faces a stage computes; positions outside that set are read
 // as zero (adj_in).
-#include "face_ops.h"
+#include <type_traits>
+
+#include "march.h"
 #include "turb_model.h"
 
 namespace uf {
@@ -332,6 +334,234 @@ __global__ __launch_bounds__(kFaceBlock) void k_advect_fwd_adj(Params<T> P, cons
   advect_fwd_adj<2>(P, U, V, W, lane_valid ? adj_in<2>(P, H2, i, j, k) : T(0), o, i, j, k, vb, sb);
   if (lane_valid) vel_store<2>(VA, o, vb, true);
   paired_scatter(GW, P.L, sb);
+}
+
+// ------------------------------------------- advection, marching along x --
+// A trace shorter than a cell scatters a face's adjoint over the 3 x 3 x 3
+// positions around the face with the hat function's weights, max(0, 1 - |m -
+// s|) per axis.  A thread marches along x and keeps the sums of its column in
+// registers, nine neighbours along y and z in each plane; the plane that is
+// complete goes to LDS, every position of the tile with its
+// halo adds the up to nine sums that concern it, and one atomic add per
+// position takes them to memory.  The scatter with eight atomic adds per
+// sample (four, where neighbouring lanes share) took 1228 us for the
+// corrector and 623 for the predictor at 256x256x64 in FP32, as LDS atomics
+// 1167 and 625 (about 160 cycles for a wavefront's ds_add_f32), these sums
+// 395 and 277 (registers and the nine writes and reads per sample bound them).
+template <int SHAPE, int NB, class T>
+struct Collect {
+  using S = MarchShape<SHAPE>;
+  static constexpr int ROWS = S::TJ + 4, PITCH = S::TKM + 4, PL = ROWS * PITCH, LDS = 9 * PL;
+  T* lds;            // [3 y][3 z][PL]: the complete plane's sums by column, zero beyond the tile
+  T sum[NB][2][9];   // of the column, before plane i is added: planes i - 1 and i
+  int own;           // the thread's column; -1: none
+  __device__ __forceinline__ void init(T* mem, bool on, int jj, int kk) {
+    lds = mem;
+    own = on ? (jj + 2) * PITCH + kk + 2 : -1;
+    for (int e = threadIdx.x; e < LDS; e += kMarch) lds[e] = T(0);
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+      for (int m = 0; m < 2; ++m)
+#pragma unroll
+        for (int q = 0; q < 9; ++q) sum[b][m][q] = T(0);
+  }
+  // Adds wbar at the position displaced by (si, sj, sk) from the face of plane
+  // i to array b; plane i - 1 is then complete and goes to LDS.
+  __device__ __forceinline__ void add(int b, T si, T sj, T sk, T wbar) {
+    const T wx[3] = {fmax(-si, T(0)), T(1) - fabs(si), fmax(si, T(0))};
+    const T wy[3] = {fmax(-sj, T(0)), T(1) - fabs(sj), fmax(sj, T(0))};
+    const T wz[3] = {fmax(-sk, T(0)), T(1) - fabs(sk), fmax(sk, T(0))};
+#pragma unroll
+    for (int y = 0; y < 3; ++y) {
+#pragma unroll
+      for (int z = 0; z < 3; ++z) {
+        const T w = wbar * wy[y] * wz[z];
+        T* u = sum[b][0] + 3 * y + z;
+        T* v = sum[b][1] + 3 * y + z;
+        if (own >= 0) lds[(3 * y + z) * PL + own] = *u + w * wx[0];
+        *u = *v + w * wx[1];
+        *v = w * wx[2];
+      }
+    }
+  }
+  // The plane in LDS added to the padded plane out.
+  template <class A>
+  __device__ __forceinline__ void flush(const A& planes, T* __restrict__ out) const {
+#pragma unroll
+    for (int v = 0; v < A::NV; ++v) {
+      if (planes.le[v] < 0) continue;
+      const int r = planes.le[v] / A::PITCH, c = planes.le[v] - r * A::PITCH;
+      const T* p = lds + r * PITCH + c;   // source (y, z) of sum (y', z') is at row r + 2 - y', column c + 2 - z'
+      T x = T(0);
+#pragma unroll
+      for (int y = 0; y < 3; ++y)
+#pragma unroll
+        for (int z = 0; z < 3; ++z) x += p[(3 * y + z) * PL + (2 - y) * PITCH + 2 - z];
+      if (x != T(0)) add_to(out + planes.off[v], x);
+    }
+  }
+};
+
+// The gradient of a near sample along the axes.
+template <class T>
+__device__ __forceinline__ void tri_grad(const Tri<T>& t, const T v[8], T grad[3]) {
+  const T ti = t.ti, tj = t.tj, tk = t.tk, ui = T(1) - ti, uj = T(1) - tj, uk = T(1) - tk;
+  grad[0] = uj * uk * (v[1] - v[0]) + tj * uk * (v[3] - v[2]) + uj * tk * (v[5] - v[4]) + tj * tk * (v[7] - v[6]);
+  grad[1] = ui * uk * (v[2] - v[0]) + ti * uk * (v[3] - v[1]) + ui * tk * (v[6] - v[4]) + ti * tk * (v[7] - v[5]);
+  grad[2] = ui * uj * (v[4] - v[0]) + ti * uj * (v[5] - v[1]) + ui * tj * (v[6] - v[2]) + ti * tj * (v[7] - v[3]);
+}
+
+template <class T>
+struct AdvectAdj {
+  const T* q[3];      // the state
+  const T* qhat[3];   // the predictor's field (corrector)
+  const T* a[3];      // adjoint of the stage's output
+  T* g[3];            // adjoint of the state
+  T* h[3];            // adjoint of qhat (corrector)
+  VelAdj<T> va;
+};
+
+// A scatter of one lane by itself (a trace that leaves the neighbouring
+// cells).
+template <class T>
+__device__ __forceinline__ void lone_scatter(T* __restrict__ qbar, const Layout& L, const Scatter8<T>& sc) {
+  if (!sc.on) return;
+  const long long SX = L.SX, PZ = L.PZ;
+  const long long lo[4] = {0, SX, PZ, SX + PZ};
+#pragma unroll
+  for (int q = 0; q < 8; ++q) add_to(qbar + sc.o + lo[q & 3] + (q >> 2), sc.w[q]);
+}
+
+// The reverse of the corrector (CORR) or the predictor of component C at the
+// faces of a tile.
+template <bool CORR, int C, int SHAPE, class T>
+__device__ __forceinline__ void march_advect_adj(const Params<T>& P, const March& G, const AdvectAdj<T>& M, T* lds,
+                                                 T* acc, int tile, int chunk) {
+  constexpr int NA = CORR ? 4 : 3, NB = CORR ? 2 : 1;
+  const Layout& L = P.L;
+  Planes<SHAPE, NA, T> A;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) A.src[a] = M.q[a];
+  if constexpr (CORR) A.src[3] = M.qhat[C];
+  Collect<SHAPE, NB, T> K;
+  T* out[NB];
+  out[0] = M.g[C];
+  if constexpr (CORR) out[1] = M.h[C];
+  int j0, k0;
+  MarchLane c = march_lane<SHAPE>(L, G, tile, L.ny - 2, L.nz + 3, L.nz + 1, L.nz + 1, j0, k0);
+  const bool on = c.active && c.k >= 0 && c.k <= L.nz;
+  A.init(L, lds, j0, k0, G.TK);
+  A.q = c.qa;
+  K.init(acc, on, c.j - j0, c.k - k0);
+  const int i0 = 1 + chunk * G.len, i1 = min(L.nx - 1, i0 + G.len);
+  A.load(i0 - 1);
+  A.store(A.s[0]);
+  A.load(i0);
+  A.store(A.s[1]);
+  A.load(i0 + 1);
+  // plane i is computed while i < i1, plane i - 1 is complete then
+  for (int i = i0; i <= i1 + 1; ++i) {
+    if (i < i1) A.store(A.s[2]);
+    lds_barrier();
+    if (i + 1 < i1) A.load(i + 2);
+    // what depends on the lane alone stays in the loop: hoisted, it spills
+    asm volatile("" : "+v"(c.j), "+v"(c.k));
+    T sc[4] = {T(0), T(0), T(0), T(0)};   // displacement and adjoint of the face's scatters
+    if (on && i < i1) {
+      const long long o = L.at(i, c.j, c.k);
+      const T ob = adj_in<C>(P, M.a[C], i, c.j, c.k);
+      T vb[3] = {T(0), T(0), T(0)};
+      if (ob != T(0)) {
+        T vel[3];
+        march_velocity<C>(A, vel);
+        const T d[3] = {vel[0] * P.dth[0], vel[1] * P.dth[1], vel[2] * P.dth[2]};
+        if (fabs(d[0]) < T(1) && fabs(d[1]) < T(1) && fabs(d[2]) < T(1)) {
+          Tri<T> tf;
+          T vf[8], gb[3];
+          march_samples(A, C, -d[0], -d[1], -d[2], tf, vf);
+          tri_grad(tf, vf, gb);
+          if constexpr (CORR) {
+            Tri<T> tb;
+            T vt[8], gf[3], mn, mx;
+            march_samples(A, 3, d[0], d[1], d[2], tb, vt);
+            tri_range(vf, mn, mx);
+            const T qt = tri_eval(tf, vf) + T(0.5) * (vel[C] - tri_eval(tb, vt));
+            if (qt < mn || qt > mx) {   // clamped: one of the eight samples
+              add_to(M.g[C] + sample_extreme<C>(L, M.q[C], i, c.j, c.k, -d[0], -d[1], -d[2], qt > mx), ob);
+            } else {
+              tri_grad(tb, vt, gf);
+              sc[3] = ob;
+#pragma unroll
+              for (int q = 0; q < 3; ++q) vb[q] = -ob * P.dth[q] * (gb[q] + T(0.5) * gf[q]);
+              vb[C] += T(0.5) * ob;
+            }
+          } else {
+            sc[3] = ob;
+#pragma unroll
+            for (int q = 0; q < 3; ++q) vb[q] = -ob * P.dth[q] * gb[q];
+          }
+#pragma unroll
+          for (int q = 0; q < 3; ++q) sc[q] = d[q];
+        } else {
+          Scatter8<T> sb, sf;
+          if constexpr (CORR) {
+            advect_corr_adj<C>(P, M.q[0], M.q[1], M.q[2], M.qhat[C], ob, M.g[C], o, i, c.j, c.k, vb, sb, sf);
+            lone_scatter(M.h[C], L, sf);
+          } else {
+            advect_fwd_adj<C>(P, M.q[0], M.q[1], M.q[2], ob, o, i, c.j, c.k, vb, sb);
+          }
+          lone_scatter(M.g[C], L, sb);
+        }
+      }
+      vel_store<C>(M.va, o, vb, !CORR);
+    }
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      if (b == 0) {
+        K.add(0, -sc[0], -sc[1], -sc[2], sc[3]);
+      } else {
+        lds_barrier();
+        K.add(b, sc[0], sc[1], sc[2], T(-0.5) * sc[3]);
+      }
+      lds_barrier();
+      K.flush(A, out[b] + (long long)i * L.SX);   // padded plane of i - 1
+    }
+    A.rotate();
+  }
+}
+
+template <bool CORR, int SHAPE, class T>
+__global__ __launch_bounds__(kMarch, 4) void k_advect_adj_march(Params<T> P, March G, AdvectAdj<T> M) {
+  __shared__ T lds[Planes<SHAPE, CORR ? 4 : 3, T>::LDS];
+  __shared__ T acc[Collect<SHAPE, CORR ? 2 : 1, T>::LDS];
+  const Layout& L = P.L;
+  int tile, chunk;
+  if (!march_block(G, tile, chunk)) return;
+  if (tile >= 0) {
+    const int C = chunk % 3;
+    if (C == 0) march_advect_adj<CORR, 0, SHAPE>(P, G, M, lds, acc, tile, chunk / 3);
+    else if (C == 1) march_advect_adj<CORR, 1, SHAPE>(P, G, M, lds, acc, tile, chunk / 3);
+    else march_advect_adj<CORR, 2, SHAPE>(P, G, M, lds, acc, tile, chunk / 3);
+    return;
+  }
+  int i = 0, j = 0, k = 0;
+  const bool valid = march_edge_corner(L, chunk * kMarch + (int)threadIdx.x, i, j, k);
+  const long long o = L.at(i, j, k);
+  auto face = [&](auto tag) {
+    constexpr int C = decltype(tag)::value;
+    const T ob = valid ? adj_in<C>(P, M.a[C], i, j, k) : T(0);
+    T vb[3];
+    Scatter8<T> sb, sf;
+    if constexpr (CORR) advect_corr_adj<C>(P, M.q[0], M.q[1], M.q[2], M.qhat[C], ob, M.g[C], o, i, j, k, vb, sb, sf);
+    else advect_fwd_adj<C>(P, M.q[0], M.q[1], M.q[2], ob, o, i, j, k, vb, sb);
+    if (valid) vel_store<C>(M.va, o, vb, !CORR);
+    paired_scatter(M.g[C], L, sb);
+    if constexpr (CORR) paired_scatter(M.h[C], L, sf);
+  };
+  face(std::integral_constant<int, 0>());
+  face(std::integral_constant<int, 1>());
+  face(std::integral_constant<int, 2>());
 }
 
 // ------------------------------------------------------------- diffusion --
@@ -1005,10 +1235,39 @@ static void launch_vel_gather(Grid& g, const Params<T>& P, void* const G[3]) {
                      (T*)G[2], n);
 }
 
+template <bool CORR, class T>
+static void launch_march_adj(Grid& g, const Params<T>& P, const AdvectAdj<T>& M) {
+  const Layout& L = P.L;
+  March G = march_geom(L.nx - 2, L.ny - 2, L.nz + 3, march_edges(L));
+  G.len = 8;   // a chunk adds two planes to its neighbours' (4 planes: 451 + 295 us, 8: 395 + 277, 16: 382 + 281)
+  G.nch = 3 * ((L.nx - 2 + G.len - 1) / G.len);   // a block computes one component
+  auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, march_grid(G), dim3(kMarch), 0, g.stream, P, G, M); };
+  if (G.shape == 0) go(k_advect_adj_march<CORR, 0, T>);
+  else if (G.shape == 1) go(k_advect_adj_march<CORR, 1, T>);
+  else go(k_advect_adj_march<CORR, 2, T>);
+}
+
 template <class T>
 void launch_advect_adj(Grid& g, const Params<T>& P, void* const Qin[3], void* const Qhat[3], void* const Aout[3],
                        void* const Gq[3], void* const Ghat[3]) {
   const dim3 grid = adj_face_grid(P.L);
+  if constexpr (sizeof(T) == 4) if (march_pays(P, kMarchFaces)) {
+    AdvectAdj<T> M;
+    for (int c = 0; c < 3; ++c) {
+      M.q[c] = (const T*)Qin[c];
+      M.qhat[c] = (const T*)Qhat[c];
+      M.a[c] = (const T*)Aout[c];
+      M.g[c] = (T*)Gq[c];
+      M.h[c] = (T*)Ghat[c];
+    }
+    M.va = vel_adj<T>(g);
+    launch_march_adj<true>(g, P, M);
+    hipLaunchKernelGGL(k_fold<T>, grid, dim3(kFaceBlock), 0, g.stream, P, (T*)Ghat[0], (T*)Ghat[1], (T*)Ghat[2]);
+    for (int c = 0; c < 3; ++c) M.a[c] = (const T*)Ghat[c];
+    launch_march_adj<false>(g, P, M);
+    launch_vel_gather<T>(g, P, Gq);
+    return;
+  }
   hipLaunchKernelGGL(k_advect_corr_adj<T>, grid, dim3(kFaceBlock), 0, g.stream, P, (const T*)Qin[0],
                      (const T*)Qin[1], (const T*)Qin[2], (const T*)Qhat[0], (const T*)Qhat[1], (const T*)Qhat[2],
                      (const T*)Aout[0], (const T*)Aout[1], (const T*)Aout[2], (T*)Gq[0], (T*)Gq[1], (T*)Gq[2],

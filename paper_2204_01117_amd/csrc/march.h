@@ -238,6 +238,74 @@ __device__ __forceinline__ void march_put(const Params<T>& P, T* __restrict__ ou
   }
 }
 
+// face_velocity() of the thread's column.
+template <int C, int SHAPE, int NA, class T>
+__device__ __forceinline__ void march_velocity(const Planes<SHAPE, NA, T>& A, T vel[3]) {
+  constexpr int ec[3] = {C == 0, C == 1, C == 2};
+#pragma unroll
+  for (int cp = 0; cp < 3; ++cp) {
+    if (cp == C) {
+      vel[cp] = A.at(cp, 0, 0, 0);
+    } else {
+      const int e[3] = {cp == 0, cp == 1, cp == 2};
+      vel[cp] = T(0.25) * (A.at(cp, -ec[0], -ec[1], -ec[2]) + A.at(cp, e[0] - ec[0], e[1] - ec[1], e[2] - ec[2]) +
+                           A.at(cp, 0, 0, 0) + A.at(cp, e[0], e[1], e[2]));
+    }
+  }
+}
+
+// Are all three displacements of every lane shorter than a cell?  The trace
+// position of a face is then within the padded array (the clamps of
+// trace_axis() do nothing: -1 < n + s < ext for 0 <= n <= ext - 1), its cell
+// is the face's or the one before it, and floor() is a comparison.  Stable
+// time steps keep it so; other wavefronts take the general path.  False for
+// a NaN.
+template <class T>
+__device__ __forceinline__ bool march_near(const T d[3]) {
+  return __all(fabs(d[0]) < T(1) && fabs(d[1]) < T(1) && fabs(d[2]) < T(1));
+}
+
+// The samples and weights of array a at the position displaced by s, near.
+template <int SHAPE, int NA, class T>
+__device__ __forceinline__ void march_samples(const Planes<SHAPE, NA, T>& A, int a, T si, T sj, T sk, Tri<T>& t, T v[8]) {
+  constexpr int PITCH = Planes<SHAPE, NA, T>::PITCH, PL = Planes<SHAPE, NA, T>::PL;
+  const bool bi = si < T(0), bj = sj < T(0), bk = sk < T(0);
+  t.ti = si + (bi ? T(1) : T(0));
+  t.tj = sj + (bj ? T(1) : T(0));
+  t.tk = sk + (bk ? T(1) : T(0));
+  const int q = A.q + (bj ? -PITCH : 0) + (bk ? -1 : 0);
+  const T* lo = A.lds + (q + (bi ? A.s[0] : A.s[1])) + a * PL;
+  const T* hi = A.lds + (q + (bi ? A.s[1] : A.s[2])) + a * PL;
+  v[0] = lo[0];
+  v[1] = hi[0];
+  v[2] = lo[PITCH];
+  v[3] = hi[PITCH];
+  v[4] = lo[1];
+  v[5] = hi[1];
+  v[6] = lo[PITCH + 1];
+  v[7] = hi[PITCH + 1];
+}
+
+// The corners beside the sides along x (i = 0, nx - 1, nx) and y (j = 0, ny -
+// 1, ny), which the tiles leave out: corner e of them.
+__host__ __device__ inline int march_edges(const Layout& L) { return 3 * (L.nz + 1) * ((L.ny + 1) + (L.nx - 2)); }
+
+__device__ __forceinline__ bool march_edge_corner(const Layout& L, int e, int& i, int& j, int& k) {
+  if (e >= march_edges(L)) return false;
+  const int r = e / (L.nz + 1);
+  k = e - r * (L.nz + 1);
+  if (r < 3 * (L.ny + 1)) {
+    const int s = r / (L.ny + 1);
+    i = s == 0 ? 0 : L.nx - 2 + s;
+    j = r - s * (L.ny + 1);
+  } else {
+    const int q = r - 3 * (L.ny + 1), s = q / (L.nx - 2);
+    j = s == 0 ? 0 : L.ny - 2 + s;
+    i = 1 + q - s * (L.nx - 2);
+  }
+  return true;
+}
+
 // The logical block of a marching launch: an edge block (tile -1, chunk its
 // number; dealt over the XCDs) or a tile of a chunk (neighbouring tiles on
 // one XCD, as xcd_block()).  False for padding blocks.

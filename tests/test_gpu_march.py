@@ -77,3 +77,51 @@ def test_march_advection_past_a_cell():
     """Displacements up to about two cells (advection alone: at such time
     steps the other stages amplify the FP32 rounding of the state)."""
     advanced((150, 240, 70), [I, O, S, S, W, S], 10.0, ("u", "v", "w"), stages=STAGE_ADVECT)
+
+
+@pytest.mark.parametrize("n,bc,scale", [
+    ((41, 100, 70), [I, O, S, S, W, S], 1.0),     # 73 lanes: a full row, one tile along z; 39 planes
+    ((26, 145, 71), [I, O, I, O, W, S], 1.0),     # 74: two tiles
+    ((60, 101, 43), [O, I, S, S, W, O], 1.0),     # the second shape
+    ((30, 450, 20), [I, O, W, S, W, S], 1.0),     # the third
+    ((41, 100, 70), [I, O, S, S, W, S], 10.0),    # displacements up to about two cells
+])
+def test_march_advection_reverse(n, bc, scale):
+    """The reverse of the advection (sums of a column in registers, planes
+    through LDS) against FP64, whose kernels scatter with atomic adds.
+
+    The waves have no plane of faces whose velocity and neighbours are
+    antisymmetric: there the limited value is its own bound, and its
+    derivative is one or the other side's by the last bit, in any precision.
+
+    FP32 rounds the values by a few 1e-7 of the largest; a face whose limiter
+    it decides otherwise (where the value is within rounding of the bound,
+    about one in 1e5) changes some fifty values entirely.  So up to 2e-3 of
+    the values may differ by more than 2e-5 of the largest; a wrong row,
+    plane or lane of the tiles is at least 4e-3 of them."""
+    import paper_2204_01117_amd as U
+    rng = np.random.default_rng(n[1])
+    out, start, lam = [], None, None
+    for dtype in ("f64", "f32"):
+        cfg = default_config(*n, 2.0, dy=2.1, dz=1.9, dt=0.05, dtype=dtype, bc=bc, u_ref=4.0, precond=PC_MG,
+                             stages=STAGE_ADVECT)
+        g = U.Grid(cfg)
+        if start is None:
+            start = []
+            for t in (g.get_field(f).cpu().double().numpy() for f in "uvw"):
+                x = [np.arange(m) / m for m in t.shape]
+                wave = (np.sin(2 * np.pi * (2 * x[0][:, None, None] + rng.uniform())) *
+                        np.sin(2 * np.pi * (3 * x[1][None, :, None] + rng.uniform())) *
+                        np.cos(np.pi * (x[2][None, None, :] + 0.13)))
+                start.append(torch.as_tensor((scale * (t + 0.3 * wave)).astype(np.float32)))
+            lam = [torch.as_tensor(rng.normal(size=tuple(t.shape)).astype(np.float32)) for t in start]
+        extra = [g.get_field(f) for f in g.adjoint_fields()[3:]]
+        cast = lambda ts: [t.to(torch.float64 if dtype == "f64" else torch.float32) for t in ts]
+        a = g.adjoint_step(cast(start) + extra, cast(lam) + [torch.zeros_like(t) for t in extra])
+        out.append([t.double().cpu() for t in a[:3]])
+        g.close()
+    for c in range(3):
+        d = (out[1][c] - out[0][c]).abs()
+        big = float((d > 2e-5 * out[0][c].abs().max()).double().mean())
+        print(n, scale, "uvw"[c], "beyond", big, "median", float(d.median() / out[0][c].abs().max()), flush=True)
+        assert big <= 2e-3
