@@ -73,10 +73,23 @@ __device__ __forceinline__ bool in_face_range(const Layout& L, int i, int j, int
   return i >= 0 && j >= 0 && k >= 0 && i <= L.nx && j <= L.ny && k <= L.nz;
 }
 
+// Value of an array at (i + di, j + dj, k + dk), zero outside the face thread
+// range; base: the array's plane i; p: the position in a plane.
+template <class T>
+struct GatherAt {
+  const Layout& L;
+  int i, j, k, p;
+  __device__ __forceinline__ T operator()(const T* __restrict__ a, int di, int dj, int dk) const {
+    const bool ok = in_face_range(L, i + di, j + dj, k + dk);
+    const int ip = i + di >= 0 && i + di <= L.nx ? i + di : i;   // uniform over the block
+    const T v = (a + (long long)(ip + 1) * L.SX)[ok ? p + dj * L.PZ + dk : p];
+    return ok ? v : T(0);
+  }
+};
+
 template <int CP, class T>
-__device__ __forceinline__ T vel_gather_value(const Layout& L, const VelAdj<T>& V, int i, int j, int k) {
-  T s = T(0);
-  if (in_face_range(L, i, j, k)) s += V.a[CP][CP][L.at(i, j, k)];
+__device__ __forceinline__ T vel_gather_value(const VelAdj<T>& V, const GatherAt<T>& at) {
+  T s = at(V.a[CP][CP], 0, 0, 0);
   const int e2[3] = {CP == 0, CP == 1, CP == 2};
 #pragma unroll
   for (int C = 0; C < 3; ++C) {
@@ -84,34 +97,33 @@ __device__ __forceinline__ T vel_gather_value(const Layout& L, const VelAdj<T>& 
     const int ec[3] = {C == 0, C == 1, C == 2};
     // faces o of component C whose average of component CP reads (i,j,k):
     // o = t + e_C, t + e_C - e_CP, t, t - e_CP
-    const int oi[4] = {i + ec[0], i + ec[0] - e2[0], i, i - e2[0]};
-    const int oj[4] = {j + ec[1], j + ec[1] - e2[1], j, j - e2[1]};
-    const int ok[4] = {k + ec[2], k + ec[2] - e2[2], k, k - e2[2]};
-    T q = T(0);
-#pragma unroll
-    for (int m = 0; m < 4; ++m)
-      if (in_face_range(L, oi[m], oj[m], ok[m])) q += V.a[C][CP][L.at(oi[m], oj[m], ok[m])];
+    T q = at(V.a[C][CP], ec[0], ec[1], ec[2]);
+    q += at(V.a[C][CP], ec[0] - e2[0], ec[1] - e2[1], ec[2] - e2[2]);
+    q += at(V.a[C][CP], 0, 0, 0);
+    q += at(V.a[C][CP], -e2[0], -e2[1], -e2[2]);
     s += T(0.25) * q;
   }
   return s;
 }
 
-// One thread per padded position: G_cp += the gathered velocity adjoint.
+// One thread per padded position, gx blocks per plane: G_cp += the gathered
+// velocity adjoint.  All 27 loads are issued at once, at clamped positions
+// (tested one by one, with 64-bit index divisions, the kernel took 138 us at
+// 256x256x64 in FP32; 59).
 template <class T>
-__global__ __launch_bounds__(256) void k_vel_gather(Params<T> P, VelAdj<T> V, T* __restrict__ G0,
-                                                    T* __restrict__ G1, T* __restrict__ G2, long long nelem) {
+__global__ __launch_bounds__(256) void k_vel_gather(Params<T> P, int gx, VelAdj<T> V, T* __restrict__ G0,
+                                                    T* __restrict__ G1, T* __restrict__ G2) {
   const Layout& L = P.L;
-  for (long long p = (long long)blockIdx.x * blockDim.x + threadIdx.x; p < nelem;
-       p += (long long)gridDim.x * blockDim.x) {
-    const int i = (int)(p / L.SX) - 1;
-    const long long r = p - (long long)(i + 1) * L.SX;
-    const int j = (int)(r / L.PZ) - 1;
-    const int k = (int)(r - (long long)(j + 1) * L.PZ) - 1;
-    if (i > L.nx + 1 || j > L.ny + 1 || k > L.nz + 1) continue;
-    G0[p] += vel_gather_value<0>(L, V, i, j, k);
-    G1[p] += vel_gather_value<1>(L, V, i, j, k);
-    G2[p] += vel_gather_value<2>(L, V, i, j, k);
-  }
+  const int pl = (int)blockIdx.x / gx, p = ((int)blockIdx.x - pl * gx) * 256 + (int)threadIdx.x;
+  if (p >= (int)L.SX) return;
+  const int jp = p / L.PZ;
+  const GatherAt<T> at{L, pl - 1, jp - 1, p - jp * L.PZ - 1, p};
+  const long long o = (long long)pl * L.SX + p;
+  const T g0 = G0[o], g1 = G1[o], g2 = G2[o];
+  const T s0 = vel_gather_value<0>(V, at), s1 = vel_gather_value<1>(V, at), s2 = vel_gather_value<2>(V, at);
+  G0[o] = g0 + s0;
+  G1[o] = g1 + s1;
+  G2[o] = g2 + s2;
 }
 
 // Cell and fractions of a trace position (i + si, j + sj, k + sk), clamped
@@ -565,58 +577,62 @@ __global__ __launch_bounds__(kMarch, 4) void k_advect_adj_march(Params<T> P, Mar
 }
 
 // ------------------------------------------------------------- diffusion --
-template <int C, class T>
-__device__ __forceinline__ T face_nu(const Params<T>& P, const T* __restrict__ nut, long long o) {
-  return P.nu + T(0.5) * (nut[o - stride<C>(P.L)] + nut[o]);
-}
-
 // Transpose of out = q + dt nu_f lap(q) at one padded position (interior
 // or ghost) of component C: the position's own row plus the rows of its
-// six neighbours.
+// six neighbours.  Loads at clamped positions, so that all are in flight.
 template <int C, class T>
 __device__ __forceinline__ T diffuse_adj_value(const Params<T>& P, const T* __restrict__ a, const T* __restrict__ nut,
-                                               int i, int j, int k) {
+                                               int i, int j, int k, long long o) {
   const Layout& L = P.L;
-  T s = T(0);
-  const T self = adj_in<C>(P, a, i, j, k);
-  if (self != T(0))
-    s += self * (T(1) - T(2) * P.dt * face_nu<C>(P, nut, L.at(i, j, k)) * (P.ih2[0] + P.ih2[1] + P.ih2[2]));
+  // adjoint of the face displaced by (di, dj, dk) (adj_in) and its viscosity
+  auto tap = [&](int di, int dj, int dk, T& nu) -> T {
+    int ext[3];
+    face_ext<C>(L, ext);
+    const int f[3] = {i + di, j + dj, k + dk};
+    bool ok = f[0] >= 0 && f[1] >= 0 && f[2] >= 0 && f[0] < ext[0] && f[1] < ext[1] && f[2] < ext[2];
+    if ((f[C] == 0 && P.bc[2 * C] != OUTLET) || (f[C] == ext[C] - 1 && P.bc[2 * C + 1] != OUTLET)) ok = false;   // fixed
+    const long long q = ok ? o + (long long)di * L.SX + (long long)dj * L.PZ + dk : L.at(0, 0, 0);
+    const T v = a[q];
+    nu = P.nu + T(0.5) * (nut[q - stride<C>(L)] + nut[q]);
+    return ok ? v : T(0);
+  };
+  T nu;
+  const T self = tap(0, 0, 0, nu);
+  T s = self != T(0) ? self * (T(1) - T(2) * P.dt * nu * (P.ih2[0] + P.ih2[1] + P.ih2[2])) : T(0);
   const int d[3][3] = {{1, 0, 0}, {0, 1, 0}, {0, 0, 1}};
 #pragma unroll
   for (int ax = 0; ax < 3; ++ax) {
 #pragma unroll
     for (int sg = -1; sg <= 1; sg += 2) {
-      const int ni = i + sg * d[ax][0], nj = j + sg * d[ax][1], nk = k + sg * d[ax][2];
-      const T an = adj_in<C>(P, a, ni, nj, nk);
-      if (an != T(0)) s += an * P.dt * face_nu<C>(P, nut, L.at(ni, nj, nk)) * P.ih2[ax];
+      const T an = tap(sg * d[ax][0], sg * d[ax][1], sg * d[ax][2], nu);
+      s += an != T(0) ? an * P.dt * nu * P.ih2[ax] : T(0);
     }
   }
   return s;
 }
 
-// One thread per padded position; every position of the three outputs is
-// written (zero outside [-1, extent] of the component).
+// One thread per padded position, gx blocks per plane; every position of the
+// three outputs is written (zero outside [-1, extent] of the component).
+// Tested tap by tap, with 64-bit index divisions, it took 154 us at
+// 256x256x64 in FP32; 131 here (63 loads a position bound it).
 template <class T>
-__global__ __launch_bounds__(256) void k_diffuse_adj(Params<T> P, const T* __restrict__ A0, const T* __restrict__ A1,
-                                                     const T* __restrict__ A2, const T* __restrict__ NUT,
-                                                     T* __restrict__ G0, T* __restrict__ G1, T* __restrict__ G2,
-                                                     long long nelem) {
+__global__ __launch_bounds__(256) void k_diffuse_adj(Params<T> P, int gx, const T* __restrict__ A0,
+                                                     const T* __restrict__ A1, const T* __restrict__ A2,
+                                                     const T* __restrict__ NUT, T* __restrict__ G0,
+                                                     T* __restrict__ G1, T* __restrict__ G2) {
   const Layout& L = P.L;
-  for (long long p = (long long)blockIdx.x * blockDim.x + threadIdx.x; p < nelem;
-       p += (long long)gridDim.x * blockDim.x) {
-    const int i = (int)(p / L.SX) - 1;
-    const long long r = p - (long long)(i + 1) * L.SX;
-    const int j = (int)(r / L.PZ) - 1;
-    const int k = (int)(r - (long long)(j + 1) * L.PZ) - 1;
-    const bool in_x = i <= L.nx, in_y = j <= L.ny, in_z = k <= L.nz;   // lower bound -1 always holds
-    // component C reaches index extent along its own axis (extent + 1 = n + 1 for the normal axis)
-    const bool r0 = (i <= L.nx + 1) && in_y && in_z;
-    const bool r1 = in_x && (j <= L.ny + 1) && in_z;
-    const bool r2 = in_x && in_y && (k <= L.nz + 1);
-    G0[p] = r0 ? diffuse_adj_value<0>(P, A0, NUT, i, j, k) : T(0);
-    G1[p] = r1 ? diffuse_adj_value<1>(P, A1, NUT, i, j, k) : T(0);
-    G2[p] = r2 ? diffuse_adj_value<2>(P, A2, NUT, i, j, k) : T(0);
-  }
+  const int pl = (int)blockIdx.x / gx, p = ((int)blockIdx.x - pl * gx) * 256 + (int)threadIdx.x;
+  if (p >= (int)L.SX) return;
+  const int jp = p / L.PZ, i = pl - 1, j = jp - 1, k = p - jp * L.PZ - 1;
+  const long long o = (long long)pl * L.SX + p;
+  const bool in_x = i <= L.nx, in_y = j <= L.ny, in_z = k <= L.nz;   // lower bound -1 always holds
+  // component C reaches index extent along its own axis (extent + 1 = n + 1 for the normal axis)
+  const T g0 = diffuse_adj_value<0>(P, A0, NUT, i, j, k, o);
+  const T g1 = diffuse_adj_value<1>(P, A1, NUT, i, j, k, o);
+  const T g2 = diffuse_adj_value<2>(P, A2, NUT, i, j, k, o);
+  G0[o] = in_y && in_z ? g0 : T(0);
+  G1[o] = in_x && in_z ? g1 : T(0);
+  G2[o] = in_x && in_y ? g2 : T(0);
 }
 
 // ------------------------------------------------------------ porosity drag
@@ -723,13 +739,53 @@ __device__ __forceinline__ void fold_face(T* __restrict__ q, const Params<T>& P,
   q[o] = acc;
 }
 
+// The corners whose faces lie on or next to a side: an axis of n cells has
+// edge_count(n) such indices 0, n - 1, n (0 and 1 for one cell), edge_index
+// the s-th, the others from 1 on.
+__host__ __device__ __forceinline__ int edge_count(int n) { return n < 2 ? 2 : 3; }
+__device__ __forceinline__ int edge_index(int n, int s) { return s == 0 ? 0 : n + 1 - edge_count(n) + s; }
+
+// Corners with an edge index along x (k fastest), then those left with one
+// along y, then those left with one along z.
+static long long fold_corners(const Layout& L) {
+  const long long ex = edge_count(L.nx), ey = edge_count(L.ny), ez = edge_count(L.nz);
+  const long long ix = L.nx + 1 - ex, iy = L.ny + 1 - ey;
+  return ex * (L.ny + 1) * (L.nz + 1) + ix * ey * (L.nz + 1) + ix * iy * ez;
+}
+
+// Only those corners have anything to fold (a thread for every corner took 41
+// us at 256x256x64, six times per reverse step; 16).
 template <class T>
 __global__ __launch_bounds__(kFaceBlock) void k_fold(Params<T> P, T* __restrict__ Q0, T* __restrict__ Q1,
-                                                     T* __restrict__ Q2) {
-  UF_FACE_THREAD(P.L);
-  if (owns_face<0, T>(P.L, i, j, k)) fold_face<0>(Q0, P, i, j, k);
-  if (owns_face<1, T>(P.L, i, j, k)) fold_face<1>(Q1, P, i, j, k);
-  if (owns_face<2, T>(P.L, i, j, k)) fold_face<2>(Q2, P, i, j, k);
+                                                     T* __restrict__ Q2, int n) {
+  const Layout& L = P.L;
+  int e = (int)blockIdx.x * kFaceBlock + (int)threadIdx.x;
+  if (e >= n) return;
+  const int ex = edge_count(L.nx), ey = edge_count(L.ny), ez = edge_count(L.nz);
+  const int ix = L.nx + 1 - ex, iy = L.ny + 1 - ey, nk = L.nz + 1;
+  const int na = ex * (L.ny + 1) * nk, nb = ix * ey * nk;
+  int i, j, k;
+  if (e < na) {
+    const int r = e / nk, s = r / (L.ny + 1);
+    k = e - r * nk;
+    i = edge_index(L.nx, s);
+    j = r - s * (L.ny + 1);
+  } else if (e < na + nb) {
+    e -= na;
+    const int r = e / nk, s = r / ix;
+    k = e - r * nk;
+    i = 1 + r - s * ix;
+    j = edge_index(L.ny, s);
+  } else {
+    e -= na + nb;
+    const int r = e / ez;
+    k = edge_index(L.nz, e - r * ez);
+    i = 1 + r / iy;
+    j = 1 + r % iy;
+  }
+  if (owns_face<0, T>(L, i, j, k)) fold_face<0>(Q0, P, i, j, k);
+  if (owns_face<1, T>(L, i, j, k)) fold_face<1>(Q1, P, i, j, k);
+  if (owns_face<2, T>(L, i, j, k)) fold_face<2>(Q2, P, i, j, k);
 }
 
 // Drag-coefficient adjoint of each cell (its face-adjacent ghosts copy it)
@@ -1229,10 +1285,9 @@ static VelAdj<T> vel_adj(const Grid& g) {
 
 template <class T>
 static void launch_vel_gather(Grid& g, const Params<T>& P, void* const G[3]) {
-  const long long n = (long long)g.nelem;
-  const int blocks = (int)std::min<long long>((n + 255) / 256, 16384);
-  hipLaunchKernelGGL(k_vel_gather<T>, dim3(blocks), dim3(256), 0, g.stream, P, vel_adj<T>(g), (T*)G[0], (T*)G[1],
-                     (T*)G[2], n);
+  const int gx = (int)((P.L.SX + 255) / 256);
+  hipLaunchKernelGGL(k_vel_gather<T>, dim3((unsigned)gx * (unsigned)(P.L.nx + 3)), dim3(256), 0, g.stream, P, gx,
+                     vel_adj<T>(g), (T*)G[0], (T*)G[1], (T*)G[2]);
 }
 
 template <bool CORR, class T>
@@ -1262,7 +1317,7 @@ void launch_advect_adj(Grid& g, const Params<T>& P, void* const Qin[3], void* co
     }
     M.va = vel_adj<T>(g);
     launch_march_adj<true>(g, P, M);
-    hipLaunchKernelGGL(k_fold<T>, grid, dim3(kFaceBlock), 0, g.stream, P, (T*)Ghat[0], (T*)Ghat[1], (T*)Ghat[2]);
+    launch_fold<T>(g, P, Ghat);
     for (int c = 0; c < 3; ++c) M.a[c] = (const T*)Ghat[c];
     launch_march_adj<false>(g, P, M);
     launch_vel_gather<T>(g, P, Gq);
@@ -1273,7 +1328,7 @@ void launch_advect_adj(Grid& g, const Params<T>& P, void* const Qin[3], void* co
                      (const T*)Aout[0], (const T*)Aout[1], (const T*)Aout[2], (T*)Gq[0], (T*)Gq[1], (T*)Gq[2],
                      (T*)Ghat[0], (T*)Ghat[1], (T*)Ghat[2], vel_adj<T>(g));
   // qhat's ghosts came from its interior faces: fold them before its reverse
-  hipLaunchKernelGGL(k_fold<T>, grid, dim3(kFaceBlock), 0, g.stream, P, (T*)Ghat[0], (T*)Ghat[1], (T*)Ghat[2]);
+  launch_fold<T>(g, P, Ghat);
   hipLaunchKernelGGL(k_advect_fwd_adj<T>, grid, dim3(kFaceBlock), 0, g.stream, P, (const T*)Qin[0],
                      (const T*)Qin[1], (const T*)Qin[2], (const T*)Ghat[0], (const T*)Ghat[1], (const T*)Ghat[2],
                      (T*)Gq[0], (T*)Gq[1], (T*)Gq[2], vel_adj<T>(g));
@@ -1282,10 +1337,10 @@ void launch_advect_adj(Grid& g, const Params<T>& P, void* const Qin[3], void* co
 
 template <class T>
 void launch_diffuse_adj(Grid& g, const Params<T>& P, void* const Aout[3], void* const Gin[3]) {
-  const long long n = (long long)g.nelem;
-  const int blocks = (int)std::min<long long>((n + 255) / 256, 16384);
-  hipLaunchKernelGGL(k_diffuse_adj<T>, dim3(blocks), dim3(256), 0, g.stream, P, (const T*)Aout[0],
-                     (const T*)Aout[1], (const T*)Aout[2], (const T*)g.NUT, (T*)Gin[0], (T*)Gin[1], (T*)Gin[2], n);
+  const int gx = (int)((P.L.SX + 255) / 256);
+  hipLaunchKernelGGL(k_diffuse_adj<T>, dim3((unsigned)gx * (unsigned)(P.L.nx + 3)), dim3(256), 0, g.stream, P, gx,
+                     (const T*)Aout[0], (const T*)Aout[1], (const T*)Aout[2], (const T*)g.NUT, (T*)Gin[0], (T*)Gin[1],
+                     (T*)Gin[2]);
 }
 
 template <class T>
@@ -1299,7 +1354,9 @@ void launch_drag_adj(Grid& g, const Params<T>& P, void* const Qin[3], void* cons
 
 template <class T>
 void launch_fold(Grid& g, const Params<T>& P, void* const A[3]) {
-  hipLaunchKernelGGL(k_fold<T>, adj_face_grid(P.L), dim3(kFaceBlock), 0, g.stream, P, (T*)A[0], (T*)A[1], (T*)A[2]);
+  const long long n = fold_corners(P.L);
+  hipLaunchKernelGGL(k_fold<T>, dim3((unsigned)((n + kFaceBlock - 1) / kFaceBlock)), dim3(kFaceBlock), 0, g.stream, P,
+                     (T*)A[0], (T*)A[1], (T*)A[2], (int)n);
 }
 
 template <class T>
