@@ -56,6 +56,10 @@ ALG_BYTES_PER_CELL = {
     "mg_rupd0": 12.5,     # marching form: read r, q; write r and the level-1 residual (1/8)
     "cg_xupd": 12.0,      # read x, d; write x (beside the coarse levels, with the marching form)
     "cg_init": 20.0,      # read u*, v*, w*, p; write r
+    "ds_row": 8.0,        # direct solve: read the residual or W; write W or z (products along z)
+    "ds_col": 8.0,        # read W; write W (products along y)
+    "ds_tri": 8.0,        # read W; write W (tridiagonal systems along x)
+    "ds_finish": 16.0,    # read r, z, x; write x
     "advect_fwd": 24.0,   # read u, v, w; write the forward-traced u, v, w
     "advect_corr": 36.0,  # read u, v, w and the traced fields; write u, v, w
     "diffuse": 28.0,      # read u, v, w, nu_t; write u, v, w
@@ -63,6 +67,11 @@ ALG_BYTES_PER_CELL = {
     "project": 28.0,      # read u*, v*, w*, p; write u, v, w
     "turbulence": 32.0,   # read u, v, w, k, omega; write k, omega, nu_t
 }
+
+# Kernels bound by the FP32 matrix cores: multiply-adds per cell are the
+# length of the axis they transform (index into the grid's sizes).
+MFMA_KERNELS = {"ds_col": 1, "ds_row": 2}
+MFMA_F32_PEAK_TFLOPS = 157.3
 
 # Per step outside the pressure iterations: the face and cell kernels and
 # the right-hand side; per CG iteration: A d, the update and one multigrid
@@ -72,8 +81,12 @@ ALG_FIXED_PER_CELL = sum(ALG_BYTES_PER_CELL[k] for k in STEP_FIXED_KERNELS)
 # (the marching form's split into mg_rupd0 + cg_xupd moves the same bytes as mg_update0)
 ALG_ITER_PER_CELL = (ALG_BYTES_PER_CELL["cg_Ad"] + ALG_BYTES_PER_CELL["mg_update0"] - ALG_BYTES_PER_CELL["mg_down0"] +
                      (ALG_BYTES_PER_CELL["mg_up0"] + ALG_BYTES_PER_CELL["mg_down0"]) * 8.0 / 7.0)
-STEP_PREFIXES = ("k_advect_", "k_diffuse", "k_drag", "k_project", "k_turbulence", "k_cg_init", "k_cg_start")
-ITER_PREFIXES = ("k_cg_Ad", "k_cg_axpy", "k_cg_xupd", "k_mg_", "k_cg_precond", "k_ai2_", "k_cg_status")
+# an iteration of the direct solve: two products along each of z and y, the
+# systems along x, the closing sweep
+ALG_DIRECT_ITER_PER_CELL = (2 * ALG_BYTES_PER_CELL["ds_row"] + 2 * ALG_BYTES_PER_CELL["ds_col"] +
+                            ALG_BYTES_PER_CELL["ds_tri"] + ALG_BYTES_PER_CELL["ds_finish"])
+STEP_PREFIXES = ("k_advect_", "k_march", "k_planes", "k_turb_march", "k_diffuse", "k_drag", "k_project", "k_turbulence", "k_cg_init", "k_cg_start")
+ITER_PREFIXES = ("k_cg_Ad", "k_cg_axpy", "k_cg_xupd", "k_mg_", "k_cg_precond", "k_ai2_", "k_cg_status", "k_ds_")
 
 # Kernels of the library by their profiler names (first match wins) and
 # the names the kernel timer and ALG_BYTES_PER_CELL use.
@@ -96,6 +109,16 @@ PROFILE_NAMES = [
     ("k_drag<", "drag"),
     ("k_project<", "project"),
     ("k_turbulence<", "turbulence"),
+    ("k_march<0", "advect_fwd"),
+    ("k_march<1", "advect_corr"),
+    ("k_planes<2", "diffuse"),
+    ("k_planes<3", "drag"),
+    ("k_project_planes<", "project"),
+    ("k_turb_march<", "turbulence"),
+    ("k_ds_row<", "ds_row"),
+    ("k_ds_col<", "ds_col"),
+    ("k_ds_tri<", "ds_tri"),
+    ("k_ds_finish<", "ds_finish"),
 ]
 
 # Calibration copy of the counter runs: bytes read (and written) once.
@@ -171,7 +194,7 @@ def step_traffic(iters_per_step, ms_per_step, ncells, tag):
     if rec.get("source_sha256") != sources_hash():
         return None
     meas = rec["bytes_fixed_per_step"] + iters_per_step * rec["bytes_per_cg_iteration"]
-    alg = (ALG_FIXED_PER_CELL + iters_per_step * ALG_ITER_PER_CELL) * ncells
+    alg = (ALG_FIXED_PER_CELL + iters_per_step * rec.get("alg_iter_per_cell", ALG_ITER_PER_CELL)) * ncells
     gbs = meas / (ms_per_step / 1e3) / 1e9
     return {"bytes_per_step": meas, "alg_bytes_per_step": alg, "achieved_GBs": gbs,
             "alg_GBs": alg / (ms_per_step / 1e3) / 1e9, "frac": gbs / HBM_PEAK_GBS,
@@ -182,9 +205,12 @@ def step_traffic(iters_per_step, ms_per_step, ncells, tag):
 # device headers every kernel includes): a counter record is stale when
 # these change, and only then.
 KERNEL_FILES = {
-    "advect_fwd": ["k_momentum.hip", "face_ops.h"], "advect_corr": ["k_momentum.hip", "face_ops.h"],
-    "diffuse": ["k_momentum.hip", "face_ops.h"], "drag": ["k_momentum.hip", "face_ops.h"],
-    "project": ["k_momentum.hip", "face_ops.h"], "turbulence": ["k_cells.hip", "turb_model.h"],
+    "advect_fwd": ["k_momentum.hip", "face_ops.h", "march.h"],
+    "advect_corr": ["k_momentum.hip", "face_ops.h", "march.h"],
+    "diffuse": ["k_momentum.hip", "face_ops.h", "march.h"], "drag": ["k_momentum.hip", "face_ops.h", "march.h"],
+    "project": ["k_momentum.hip", "face_ops.h", "march.h"],
+    "turbulence": ["k_cells.hip", "turb_model.h", "face_ops.h", "march.h"],
+    "ds_row": ["k_direct.hip"], "ds_col": ["k_direct.hip"], "ds_tri": ["k_direct.hip"], "ds_finish": ["k_direct.hip"],
     "cg_Ad": ["k_pressure.hip"], "cg_axpy": ["k_pressure.hip"], "cg_init": ["k_pressure.hip"],
     "mg_up0": ["k_mg.hip"], "mg_down0": ["k_mg.hip"], "mg_update0": ["k_mg.hip"], "mg_rupd0": ["k_mg.hip"],
     "cg_xupd": ["k_mg.hip"],
@@ -308,7 +334,7 @@ def traffic_summary(run_dir, command, out_dir=None, name="C2"):
         bn = profile_name(name)
         if bn is None or (name, grid) not in write:
             continue
-        if bn not in best or grid > best[bn][1]:
+        if bn not in best or fetch[(name, grid)] > fetch[best[bn]]:   # the full grid's, of the kernels that share a name
             best[bn] = (name, grid)
     # the first restriction of a solve, when tiled: the largest tiled restriction
     if "mg_down0" not in best:
@@ -345,14 +371,21 @@ def traffic_summary(run_dir, command, out_dir=None, name="C2"):
                 tot["iter"] += v * 1024.0 / factor
     for name, _, _ in fd:
         n = short(name)
-        steps += n.startswith("k_advect_fwd")
+        steps += n.startswith(("k_advect_fwd", "k_march<0"))
         iters += n.startswith("k_cg_Ad")
+    # direct solves: the iterations of products (a launch that found the solve
+    # finished reads next to nothing); sweeps between them count into these
+    tri = [v for name, _, v in fd if short(name).startswith("k_ds_tri")]
+    direct = bool(tri) and not iters
+    if direct:
+        iters = sum(v >= 0.05 * max(tri) for v in tri)
+    alg_iter = ALG_DIRECT_ITER_PER_CELL if direct else ALG_ITER_PER_CELL
     step_rec = {
         "workload": tag, "steps": steps, "cg_iterations": iters,
         "bytes_fixed_per_step": tot["step"] / max(steps, 1),
         "bytes_per_cg_iteration": tot["iter"] / max(iters, 1),
         "alg_bytes_fixed_per_step": ALG_FIXED_PER_CELL * ncell,
-        "alg_bytes_per_cg_iteration": ALG_ITER_PER_CELL * ncell,
+        "alg_bytes_per_cg_iteration": alg_iter * ncell, "alg_iter_per_cell": alg_iter,
         "calibration": {"fetch_factor": f_fetch, "write_factor": f_write},
         "source_sha256": sources_hash(), "command": command,
     }
@@ -962,6 +995,12 @@ def main():
     alg_bytes = ALG_BYTES_PER_CELL[dominant] * ncells
     avg_s = k_ms / 1e3 / max(k_n, 1)        # over every launch, as rocprof averages
     achieved = alg_bytes / avg_s / 1e9
+    roofline = {"bound": "hbm", "kernel": dominant, "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
+                "frac": achieved / HBM_PEAK_GBS}
+    if dominant in MFMA_KERNELS:
+        tf = 2.0 * (nx, ny, nz)[MFMA_KERNELS[dominant]] * ncells / avg_s / 1e12
+        roofline = {"bound": "mfma", "kernel": dominant, "achieved": tf, "peak": MFMA_F32_PEAK_TFLOPS,
+                    "unit": "TFLOP/s", "frac": tf / MFMA_F32_PEAK_TFLOPS}
     result = {
         "metric": "cell-updates/s per full RANS step (incl. pressure solve)",
         "value": ncells * args.steps / secs,
@@ -980,11 +1019,8 @@ def main():
                    "turbulence": "k-omega"},
         "cg_iters_per_step": iters / args.steps,
         "cg_iters_max": st.get("cg_iters_max"),
-        "roofline": {"bound": "hbm", "kernel": dominant, "achieved": achieved, "peak": HBM_PEAK_GBS,
-                     "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
-                     "traffic": traffic_for(dominant, tag),
-                     "avg_launch_us": avg_s * 1e6, "launches": k_n,
-                     "alg_bytes_per_launch": alg_bytes},
+        "roofline": dict(roofline, traffic=traffic_for(dominant, tag), avg_launch_us=avg_s * 1e6, launches=k_n,
+                         alg_bytes_per_launch=alg_bytes),
         "diagnostics": {"max_div_per_s": st.get("max_div"), "max_cfl": st.get("max_cfl"),
                         "nut_clip_frac": st.get("nut_clip_frac")},
     }

@@ -1,7 +1,7 @@
 // Cell-centred kernels: the k-omega turbulence update (Sec. 3, solved after
 // the projection), the porosity -> drag-coefficient map (Sec. 3 drag law),
-// boundary refresh of cell fields and packing between the padded storage
-// and the compact layouts of the C ABI.
+// and packing between the padded storage (boundary rules applied as values
+// are put in) and the compact layouts of the C ABI.
 #include "march.h"
 #include "turb_model.h"
 
