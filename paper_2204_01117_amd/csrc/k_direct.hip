@@ -650,6 +650,9 @@ static DsGeom ds_geom(const Layout& L) {
   const int tiles = d.njt * d.nkt;
   const int want = std::max(1, std::min((L.nx + 3) / 4, (1024 + tiles - 1) / tiles));
   d.nfi = (L.nx + want - 1) / want;
+  // few blocks: a chunk's own length is what takes the time (64x32x16 10.6 ->
+  // 9.2 us; 96x80x48 in FP64, 144 blocks, 14.4 -> 15.2)
+  if (tiles * want < 64) d.nfi = std::max(1, d.nfi / 2);
   d.gy = (L.nx + d.nfi - 1) / d.nfi;
   return d;
 }
@@ -759,7 +762,10 @@ static void launch_row(Grid& g, const T* in, T* out, const T* E, long long ldw) 
     launch_k(g, kernel, xcd_grid(nt, mt), dim3(kDsThreads), L, in, out, E, lde, ldw, mt, nt, (const CgState*)g.st);
   };
   constexpr int MT = Mfma<T>::MT;
-  if (L.nz > 2 * MT) go(k_ds_row<T, 2, 2, FWD>, 4 * MT, 4 * MT);
+  // few rows: the small tile, for the blocks (64x32x16 6.9 -> 4.8 us a launch,
+  // 129x97x35 10.1 -> 6.5, 96x80x48 in FP64 7.4 -> 6.0)
+  if (M < 256 * 4 * MT) go(k_ds_row<T, 1, 1, FWD>, 2 * MT, 2 * MT);
+  else if (L.nz > 2 * MT) go(k_ds_row<T, 2, 2, FWD>, 4 * MT, 4 * MT);
   else go(k_ds_row<T, 2, 1, FWD>, 4 * MT, 2 * MT);
 }
 
