@@ -161,7 +161,8 @@ struct CellDiv {
 // all in flight together (251 -> 146 us at 512x512x128, 28 -> 20 at 256x256x64).
 constexpr int kInitCells = 4;
 
-template <class T>
+// DIFF false (the CG): D x minus the neighbours' sum, as its iterations form A d.
+template <bool DIFF, class T>
 __global__ __launch_bounds__(kCgBlock) void k_cg_init(Params<T> P, const T* __restrict__ U, const T* __restrict__ V,
                                                       const T* __restrict__ W, const T* __restrict__ bin,
                                                       const T* __restrict__ X, T* __restrict__ R, CgCtl c, int ilen) {
@@ -169,9 +170,12 @@ __global__ __launch_bounds__(kCgBlock) void k_cg_init(Params<T> P, const T* __re
   UF_CG_RANGE(L, ilen);
   double v[2] = {0.0, 0.0};
   if (i0 < i1) {
-    const long long ym = j == 0 && P.bc[2] != OUTLET ? 0 : -L.PZ, yp = j == L.ny - 1 && P.bc[3] != OUTLET ? 0 : L.PZ;
-    const long long zm = k == 0 && P.bc[4] != OUTLET ? 0 : -1, zp = k == L.nz - 1 && P.bc[5] != OUTLET ? 0 : 1;
+    const long long ym = DIFF && j == 0 && P.bc[2] != OUTLET ? 0 : -L.PZ;
+    const long long yp = DIFF && j == L.ny - 1 && P.bc[3] != OUTLET ? 0 : L.PZ;
+    const long long zm = DIFF && k == 0 && P.bc[4] != OUTLET ? 0 : -1;
+    const long long zp = DIFF && k == L.nz - 1 && P.bc[5] != OUTLET ? 0 : 1;
     const CellDiv<T> div(P, j, k);
+    const T dyz = diag_yz(P, j, k);
     const long long o0 = L.at(i0, j, k);
     T xm = X[o0 - L.SX], xc = X[o0], u0 = bin ? T(0) : U[o0];
     for (int i = i0; i < i1; i += kInitCells) {
@@ -200,8 +204,15 @@ __global__ __launch_bounds__(kCgBlock) void k_cg_init(Params<T> P, const T* __re
         const T b = bin ? f[q][0] : -P.rho_dt * div.of(P, u0, f[q][0], f[q][1], f[q][2], f[q][3], f[q][4], i + q);
         const T wm = i + q == 0 && P.bc[0] != OUTLET ? T(0) : P.ih2[0];
         const T wp = i + q == L.nx - 1 && P.bc[1] != OUTLET ? T(0) : P.ih2[0];
-        const T r = b + (wm * (xm - xc) + wp * (xp[q] - xc) + P.ih2[1] * ((n[q][0] - xc) + (n[q][1] - xc)) +
-                         P.ih2[2] * ((n[q][2] - xc) + (n[q][3] - xc)));
+        T r;
+        if constexpr (DIFF) {
+          r = b + (wm * (xm - xc) + wp * (xp[q] - xc) + P.ih2[1] * ((n[q][0] - xc) + (n[q][1] - xc)) +
+                   P.ih2[2] * ((n[q][2] - xc) + (n[q][3] - xc)));
+        } else {
+          const T ax = (dyz + diag_x(P, i + q)) * xc - (xp[q] + xm) * P.ih2[0] - (n[q][0] + n[q][1]) * P.ih2[1] -
+                       (n[q][2] + n[q][3]) * P.ih2[2];
+          r = b - ax;
+        }
         R[o0 + (long long)(i + q - i0) * L.SX] = r;
         v[0] += (double)b * (double)b;
         v[1] += (double)r * (double)r;
@@ -571,8 +582,12 @@ void launch_cg_start(Grid& g, const Params<T>& P, void* const Qs[3], const void*
   const CgCtl c = make_ctl(g);
   {
     TimedLaunch tl(g, UF_TK_CG_INIT);
-    launch_k(g, k_cg_init<T>, cl.grid, dim3(kCgBlock), P, (const T*)Qs[0], (const T*)Qs[1],
-                     (const T*)Qs[2], (const T*)b, (const T*)g.X, (T*)resid(g, 0), c, cl.ilen);
+    auto go = [&](auto kernel) {
+      launch_k(g, kernel, cl.grid, dim3(kCgBlock), P, (const T*)Qs[0], (const T*)Qs[1], (const T*)Qs[2], (const T*)b,
+               (const T*)g.X, (T*)resid(g, 0), c, cl.ilen);
+    };
+    if (g.direct) go(k_cg_init<true, T>);
+    else go(k_cg_init<false, T>);
   }
   hipLaunchKernelGGL(k_cg_start, dim3(1), dim3(256), 0, g.stream, c, g.cfg.cg_tol);
   hipLaunchKernelGGL(k_cg_restart<T>, cl.grid, dim3(kCgBlock), 0, g.stream, P, (const T*)Qs[0], (const T*)Qs[1],
