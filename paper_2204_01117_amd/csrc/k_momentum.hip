@@ -14,6 +14,9 @@
 namespace uf {
 
 // ------------------------------------------------------------- advection --
+// A NaN velocity clamps the trace to position -1, where the sample is finite:
+// every path adds nan_if(), so that such a face is NaN in the predictor's
+// field too.
 template <int C, class T>
 __device__ __forceinline__ T advect_fwd_value(const Params<T>& P, const T* __restrict__ U, const T* __restrict__ V,
                                               const T* __restrict__ W, long long o, int i, int j, int k) {
@@ -22,7 +25,8 @@ __device__ __forceinline__ T advect_fwd_value(const Params<T>& P, const T* __res
   const T* q = C == 0 ? U : (C == 1 ? V : W);
   T mn, mx;
   return sample<C, false>(P.L, q, i, j, k, -(vel[0] * P.dth[0]), -(vel[1] * P.dth[1]), -(vel[2] * P.dth[2]), &mn,
-                          &mx);
+                          &mx) +
+         nan_if<T>(any_nan3(vel));
 }
 
 template <int C, class T>
@@ -39,7 +43,7 @@ __device__ __forceinline__ T advect_corr_value(const Params<T>& P, const T* __re
   T d0, d1;
   const T qc = sample<C, false>(P.L, qhat, i, j, k, di, dj, dk, &d0, &d1);
   const T qt = qh + T(0.5) * (q[o] - qc);
-  return nmin(nmax(qt, mn), mx);
+  return nmin(nmax(qt, mn), mx) + nan_if<T>(any_nan3(vel));
 }
 
 template <class T>
