@@ -48,9 +48,21 @@ def voxelize(n, h, verts, tris, tri_begin, phi_obj, sub=4, dtype="f32", device="
     return out
 
 
+def _row_values(rows):
+    """The values of the rows, one after another, in float64: at once where numpy takes the rows as a table, else
+    by float() (rows that are tensors on the GPU or require grad, rows of unequal length)."""
+    try:
+        table = np.array(rows, dtype=np.float64)
+    except (TypeError, ValueError, RuntimeError):
+        table = None
+    if table is None or (table.size and table.ndim != 2):
+        table = np.array([float(v) for row in rows for v in row], dtype=np.float64)
+    return table.ravel()
+
+
 def _smooth_objects(n, h, boxes, cylinders, width):
     """uf_smooth_objects and the host arrays it points to."""
-    bk, ck = (np.array(rows, dtype=np.float64).ravel() for rows in (boxes, cylinders))
+    bk, ck = _row_values(boxes), _row_values(cylinders)
     o = L.uf_smooth_objects()
     o.nx, o.ny, o.nz = (int(x) for x in n)
     o.dx, o.dy, o.dz = (float(x) for x in h)
