@@ -78,9 +78,11 @@ class Grid:
         """``set_field`` for every field of ``st``, waiting once before and once after them."""
         ts = [(f, self._dev(a, self.extent(f))) for f, a in st.items() if f != "phi"]
         self.torch.cuda.current_stream(self.device).synchronize()
-        for f, t in ts:
-            L.check(L.uf_set_field(self.handle, L.FIELD_IDS[f], c_void_p(t.data_ptr())))
-        self.tstream.synchronize()
+        try:
+            for f, t in ts:
+                L.check(L.uf_set_field(self.handle, L.FIELD_IDS[f], c_void_p(t.data_ptr())))
+        finally:   # also on an error: the fields before it are still read from ts
+            self.tstream.synchronize()
 
     def step(self, nsteps=1, stats=True, allow=()):
         s = L.uf_step_stats()
