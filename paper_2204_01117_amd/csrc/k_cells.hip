@@ -167,8 +167,8 @@ __device__ __forceinline__ void turb_march(const Params<T>& P, const March& G, c
 }
 
 template <int SHAPE, class T>
-__global__ __launch_bounds__(kMarch, sizeof(T) == 4 ? 6 : 2) void k_turb_march(Params<T> P, March G, TurbArgs<T> M,
-                                                                              const int* __restrict__ gate) {
+__global__ __launch_bounds__(kMarch, 6) void k_turb_march(Params<T> P, March G, TurbArgs<T> M,
+                                                           const int* __restrict__ gate) {
   __shared__ T lds[Planes<SHAPE, 5, T>::LDS];
   if (gate && !*gate) return;
   int tile, chunk;
@@ -371,7 +371,7 @@ template <class T>
 void launch_turb(Grid& g, const Params<T>& P, void* const Q[3], const void* K0, const void* W0, void* K1, void* W1,
                  void* NUT, int update_kw, const int* gate) {
   TimedLaunch tl(g, UF_TK_TURB);
-  if (update_kw && march_pays(P, kMarchTurb)) {
+  if constexpr (sizeof(T) == 4) if (update_kw && march_pays(P, kMarchTurb)) {
     const Layout& L = P.L;
     const TurbArgs<T> M{{(const T*)Q[0], (const T*)Q[1], (const T*)Q[2], (const T*)K0, (const T*)W0},
                         {(T*)K1, (T*)W1, (T*)NUT}, nf_word(g)};

@@ -377,7 +377,7 @@ __device__ __forceinline__ void march_edge(const Params<T>& P, const MarchArgs<T
 }
 
 template <int STAGE, int SHAPE, class T>
-__global__ __launch_bounds__(kMarch, sizeof(T) == 4 ? 6 : 2) void k_march(Params<T> P, March G, MarchArgs<T> M) {
+__global__ __launch_bounds__(kMarch, 6) void k_march(Params<T> P, March G, MarchArgs<T> M) {
   __shared__ T lds[Planes<SHAPE, march_arrays(STAGE), T>::LDS];
   int tile, chunk;
   if (!march_block(G, tile, chunk)) return;
@@ -758,7 +758,7 @@ static void launch_split(Grid& g, const Params<T>& P, void* const Q[3], const vo
 template <class T>
 void launch_advect(Grid& g, const Params<T>& P, void* const Qin[3], void* const Qhat[3], void* const Qout[3]) {
   const dim3 grid = face_grid(P.L);
-  if (march_pays(P, kMarchFaces)) {
+  if constexpr (sizeof(T) == 4) if (march_pays(P, kMarchFaces)) {
     {
       TimedLaunch tl(g, UF_TK_ADVECT_FWD);
       launch_march<MS_ADVECT_FWD, T>(g, P, Qin, nullptr, Qhat);
