@@ -322,8 +322,8 @@ uf_status uf_step_batch(const uf_grid* grids, int32_t n, int32_t nsteps, uf_step
  * predictor and corrector, diffusion, drag, projection) and the k-omega
  * update is one kernel walking a single queue of every case's blocks.
  * Each case's pressure solve (its start from the drag output and a
- * captured number of CG iterations -- the last solve's count plus two;
- * iterations past convergence return at once) is a hipGraph of its own,
+ * captured number of iterations -- the last solve's count, plus two for
+ * the CG; iterations past convergence return at once) is a hipGraph of its own,
  * replayed on the case's own stream so that the cases' solves overlap; the
  * face stages before it and the projection and k-omega update after it are
  * two more hipGraphs.  Between the solves and the back half the host reads

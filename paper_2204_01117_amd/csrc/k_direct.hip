@@ -673,8 +673,12 @@ static int ds_chunk(int nx) {
 
 // Which solves are direct: the multigrid configuration with the residual
 // criterion (the paper's criterion and the preconditioner study iterate),
-// lines of x that the tridiagonal kernel holds, and axes short enough for
-// dense products to be the cheaper way.
+// lines of x that the tridiagonal kernel holds, and axes up to the longest
+// measured.  There the products are still far the cheaper way (a solve from
+// zero, ms, CG against direct; the CG takes 9 to 20 iterations in FP32, 18 to
+// 23 in FP64): 8x1024x1000 4.87 against 1.10, 64x64x1900 4.04 / 1.00,
+// 4x40x2000 0.99 / 0.26, 200x1000x1000 128 / 18; FP64 64x1000x1000 93 / 11,
+// 16x1900x128 6.7 / 1.1, 4x40x2000 3.7 / 0.35.
 bool direct_use(const uf_config& c, size_t esize) {
   const double bytes = (double)(c.nx + 3) * (c.ny + 3) * (c.nz + 3) * (double)esize;
   return c.precond == UF_PC_MG && c.cg_criterion == 0 && ds_chunk(c.nx) > 0 && c.ny + c.nz <= 2048 &&

@@ -619,9 +619,10 @@ struct PressureSwap {
   }
 };
 
-// The reverse step's own solve iterates with the CG: its result is a
-// gradient, held in FP64 for the porosity, that callers compare between
-// runs, and the CG's iterate differs from the direct one by the tolerance.
+// The reverse step's own solve iterates with the CG.  Its result is a
+// gradient, held in FP64 for the porosity; the direct solve's differs from
+// it by about the solve's tolerance (1.2e-6 of phibar at 256x256x64), and
+// which of the two lies closer to the FP64 reverse step is not measured.
 struct IterativeSolve {
   Grid& g;
   const bool was;
